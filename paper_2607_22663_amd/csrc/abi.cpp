@@ -646,7 +646,7 @@ mbe_status threshold_update_launch(const void *logits, int64_t rows, int64_t voc
   p.block_size = block_size;
   p.omega_mask = omega_mask;
   p.gate = run_if_nonzero;
-  const bool vec = (reinterpret_cast<uintptr_t>(logits) % 16 == 0) && (row_stride % 8 == 0);
+  const bool vec = reinterpret_cast<uintptr_t>(logits) % 2 == 0;   // rows may start anywhere on 2 bytes
   hipError_t e = launch_threshold_update(p, vec, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "threshold update launch");
   return MBE_OK;
@@ -755,7 +755,7 @@ mbe_status mbe_edit_select(const void *logits, int64_t rows, int64_t vocab, int6
     char *ws = static_cast<char *>(workspace);
     p.partials = reinterpret_cast<mbe::EsPartial *>(ws);
   }
-  const bool vec = (reinterpret_cast<uintptr_t>(logits) % 16 == 0) && (row_stride % 8 == 0);
+  const bool vec = reinterpret_cast<uintptr_t>(logits) % 2 == 0;   // rows may start anywhere on 2 bytes
   hipError_t e = mbe::launch_edit_select(p, vec, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "edit select launch");
   return MBE_OK;

@@ -24,6 +24,18 @@
 // chunk maximum re-read their iteration it_max to find its first index, and a
 // min over the workgroup picks the lowest.  This keeps the argmax bookkeeping
 // out of the per-element loop at the cost of a few cache lines per chunk.
+//
+// What bounds it: HBM, with the VALU close behind (64 logits cost about 32
+// cycles of a SIMD, half of them the exponential, 36 with the entropy; at
+// 6.8 TB/s a SIMD has 40).  So the loop keeps no per-iteration copies (two
+// register sets in turn) and forms the reference only when the maximum moves:
+// 2048 x 131072 with entropy 99.6 -> 95.5 us for the whole update, 512 x
+// 131072 without 27.0 -> 25.5 us, 8192 x 131072 313.9 -> 312.5 us (6.87 TB/s).
+// Every row takes 16-byte loads wherever it starts (its up to 7 logits before
+// and after the 16-byte grid are read one per thread): 992 rows of 100003
+// packed behind each other, with entropy, 276.7 -> 48.4 us; and an iteration
+// that is not whole no longer sends the chunk through a second pass: 1024 x
+// 32000 39.8 -> 34.2 us.
 // Rows split over several workgroups (few rows) write partials that a small
 // finalize kernel merges in chunk order, so results are bitwise reproducible.
 #include <hip/hip_runtime.h>
@@ -37,6 +49,10 @@ namespace mbe {
 namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// Logits in global memory: said in the type, since an address made from a
+// row's start and its offset on the 16-byte grid would otherwise be loaded
+// with flat instructions.
+typedef const __attribute__((address_space(1))) uint16_t g_bf16;
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kU = kEsVecPerThread;
@@ -44,7 +60,7 @@ constexpr int kT = kEsThreads;
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-__device__ __forceinline__ float bf16_at(const uint16_t *p) {
+__device__ __forceinline__ float bf16_at(g_bf16 *p) {
   return __uint_as_float(static_cast<uint32_t>(*p) << 16);
 }
 
@@ -139,6 +155,10 @@ __device__ __forceinline__ float max_iter(const float (&x)[kU][8]) {
   return v[0];
 }
 
+__device__ __forceinline__ uint32_t load16b(g_bf16 *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
 // Eight bf16 logits of one 16-byte vector as floats.
 __device__ __forceinline__ void unpack8(const u32x4 &w, float x[8]) {
 #pragma unroll
@@ -150,22 +170,26 @@ __device__ __forceinline__ void unpack8(const u32x4 &w, float x[8]) {
 
 // Streaming load of one 16-byte vector: each logit is read once, so it is
 // not kept in cache.
-__device__ __forceinline__ u32x4 load16(const uint16_t *row, int64_t unit) {
-  return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row + unit * 8));
+__device__ __forceinline__ u32x4 load16(g_bf16 *grid, int64_t unit) {
+  return __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4 *)(grid + unit * 8));
 }
 
-// Loads vector unit `unit` (elements 8*unit .. 8*unit+7) as 8 floats; elements
-// at or beyond `end` read as -inf.
+// Vector unit `unit` (elements 8*unit .. 8*unit+7 from `grid`) as 8 floats.
+// VEC: one 16-byte load of a whole unit.  Otherwise (logits on an odd address)
+// one logit at a time; elements at or beyond `end` read as -inf.
 template <bool VEC>
-__device__ __forceinline__ void load_unit(const uint16_t *row, int64_t unit, int64_t end, float x[8]) {
-  const int64_t e0 = unit * 8;
-  if (VEC && e0 + 8 <= end) {
-    unpack8(load16(row, unit), x);
+__device__ __forceinline__ void load_unit(g_bf16 *grid, int64_t unit, int64_t end, float x[8]) {
+  if constexpr (VEC) {
+    unpack8(load16(grid, unit), x);
   } else {
+    const int64_t e0 = unit * 8;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) x[k] = (e0 + k < end) ? bf16_at(row + e0 + k) : -INFINITY;
+    for (int k = 0; k < 8; ++k) x[k] = (e0 + k < end) ? bf16_at(grid + e0 + k) : -INFINITY;
   }
 }
+
+// it_max of a thread whose maximum is its logit of the row's head or tail
+constexpr int32_t kHeadIter = -2, kTailIter = -3;
 
 // The token-to-token decision for one row from its (max, argmax, sum), or,
 // for the threshold update, the row's prediction, confidence and entropy.
@@ -201,32 +225,54 @@ __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
   const int64_t row = wg / p.chunks;
   const int32_t chunk = static_cast<int32_t>(wg % p.chunks);
   const int tid = threadIdx.x;
-  const uint16_t *rowp = p.logits + row * p.ld;
-  const int64_t c0 = static_cast<int64_t>(chunk) * p.chunk_len;
-  const int64_t c1 = min(p.vocab, c0 + p.chunk_len);
-  const int64_t u0 = c0 / 8;
-  const int64_t u1 = (c1 + 7) / 8;
+  g_bf16 *rowp = (g_bf16 *)(p.logits) + row * p.ld;
+  // Units of 8 logits on the 16-byte grid of the addresses.  A row that starts
+  // off the grid (an odd vocabulary with packed rows, a padded stride, a view)
+  // has a head of up to 7 logits before its first whole unit, and any row a
+  // tail of up to 7 after its last.  Both are read one logit per thread (by
+  // the first and the last chunk), the units between with vector loads, and
+  // no load leaves the row.
+  const int off = VEC ? static_cast<int>((reinterpret_cast<uintptr_t>(p.logits + row * p.ld) >> 1) & 7) : 0;
+  g_bf16 *grid = rowp - off;                          // dereferenced inside the row only
+  const int64_t g_end = p.vocab + off;                // row's end on the grid
+  const bool last = chunk + 1 == p.chunks;
+  const int head = VEC && off != 0 && chunk == 0 ? static_cast<int>(min(static_cast<int64_t>(8 - off), p.vocab)) : 0;
+  const int tail = VEC && last && (g_end >= 8 || off == 0) ? static_cast<int>(g_end & 7) : 0;
+  const int64_t tail0 = g_end - tail - off;           // the tail's first index
+  const int64_t chunk_units = p.chunk_len / 8;
+  const int64_t u0 = chunk * chunk_units + (head ? 1 : 0);
+  const int64_t u1 = last ? (VEC ? g_end / 8 : (g_end + 7) / 8) : (chunk + 1) * chunk_units;
+  const int64_t c1 = min(g_end, u1 * 8);              // end of the units' logits on the grid
+
+  // This thread's logit of the head and of the tail, if it has one: requested
+  // before the first vectors by every workgroup (a branch around the loads
+  // would wait for them in it) and used after them.  Relaxed atomic loads
+  // stay where they are written; every address lies in the row.
+  uint32_t raw_h = 0, raw_t = 0;
+  if constexpr (VEC) {
+    raw_h = load16b(rowp + min(static_cast<int64_t>(tid), p.vocab - 1));
+    raw_t = load16b(rowp + min(tail0 + tid, p.vocab - 1));
+  }
 
   float m = -INFINITY, s = 0.f, t = 0.f;
+  float nref = 0.f;      // -ref_of(m), 0 while m is -inf
   int32_t it_max = -1;
   int32_t it = 0;
   // One iteration's 16 logits of this thread into the running (m, s, t).
   auto accumulate = [&](const float (&x)[kU][8], auto clamp) {
     const float cm = max_iter(x);
     if (cm > m) {
-      if (m == -INFINITY) {
-        s = 0.f;
-        t = 0.f;
-      } else {
-        const float d = ref_of(m) - ref_of(cm);
+      const float ref = ref_of(cm);
+      if (m != -INFINITY) {     // (while m is -inf, s = t = 0)
+        const float d = -nref - ref;
         const float f = __builtin_amdgcn_exp2f(d);
         if (ENT) t = f * __builtin_fmaf(d, s, t);
         s *= f;
       }
       m = cm;
+      nref = -ref;
       it_max = it;
     }
-    const float nref = (m == -INFINITY) ? 0.f : -ref_of(m);
     float acc = 0.f, acct = 0.f;
 #pragma unroll
     for (int j = 0; j < kU; ++j)
@@ -241,49 +287,98 @@ __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
     s += acc;
     if (ENT) t += acct;
   };
-  // The whole chunk: iterations whose units all lie inside the chunk with
-  // unguarded vector loads, the next iteration's loads issued before the
-  // current one is reduced; then at most one guarded iteration.
+  // The whole chunk, the next iteration's loads issued before the current
+  // one is reduced.
   auto pass = [&](auto clamp) {
     m = -INFINITY;
     s = 0.f;
     t = 0.f;
+    nref = 0.f;
     it_max = -1;
     it = 0;
-    constexpr int64_t per_iter = kT * kU;
-    int64_t base = u0;
+    constexpr int32_t per_iter = kT * kU;
+    // a thread's one logit of the head (visited first: the row's lowest
+    // indices) or of the tail (visited last)
+    auto single = [&](float x, int32_t mark) {
+      if (x > m) {
+        const float ref = ref_of(x);
+        if (m != -INFINITY) {
+          const float d = -nref - ref;
+          const float f = __builtin_amdgcn_exp2f(d);
+          if (ENT) t = f * __builtin_fmaf(d, s, t);
+          s *= f;
+        }
+        m = x;
+        nref = -ref;
+        it_max = mark;
+      }
+      if (x != -INFINITY) {
+        const float y = __builtin_fmaf(x, kLog2e, nref);
+        const float e = __builtin_amdgcn_exp2f(y);
+        s += e;
+        if (ENT) t = __builtin_fmaf(e, y, t);
+      }
+    };
     if constexpr (VEC) {
-      const int64_t u_full = c1 / 8;      // units [u0, u_full) hold 8 logits of the chunk each
-      const int64_t n_full = u_full > u0 ? (u_full - u0) / per_iter : 0;
-      if (n_full > 0) {
-        u32x4 w[kU];
+      // Iterations 0 .. n - 1 of per_iter units, the last perhaps of fewer.  A
+      // request past the last unit reads the last one again, so that
+      // every request is unconditional (the compiler would otherwise wait for
+      // all loads in flight where a skipped request and a made one meet).  Two
+      // register sets in turn, so that no vector is copied.
+      const int32_t units = static_cast<int32_t>(max(u1 - u0, static_cast<int64_t>(0)));
+      const int32_t n_full = units / per_iter, n = (units + per_iter - 1) / per_iter;
+      u32x4 wa[kU], wb[kU];
+      auto request = [&](u32x4 (&w)[kU], int32_t i) {
 #pragma unroll
-        for (int j = 0; j < kU; ++j) w[j] = load16(rowp, base + j * kT + tid);
-        for (int64_t i = 0; i < n_full; ++i, base += per_iter, ++it) {
-          float x[kU][8];
+        for (int j = 0; j < kU; ++j) w[j] = load16(grid, u0 + min(i * per_iter + j * kT + tid, units - 1));
+      };
+      auto reduce_iter = [&](const u32x4 (&w)[kU], auto partial) {
+        float x[kU][8];
 #pragma unroll
-          for (int j = 0; j < kU; ++j) unpack8(w[j], x[j]);
-          if (i + 1 < n_full) {
+        for (int j = 0; j < kU; ++j) {
+          unpack8(w[j], x[j]);
+          if constexpr (decltype(partial)::value) {
+            if (it * per_iter + j * kT + tid >= units) {
 #pragma unroll
-            for (int j = 0; j < kU; ++j) w[j] = load16(rowp, base + per_iter + j * kT + tid);
+              for (int k = 0; k < 8; ++k) x[j][k] = -INFINITY;
+            }
           }
-          accumulate(x, clamp);
         }
+        // clamped: the missing units' -inf must not reach the entropy sum
+        if constexpr (decltype(partial)::value) accumulate(x, std::true_type{});
+        else accumulate(x, clamp);
+        ++it;
+      };
+      if (n > 0) request(wa, 0);
+      if (tid < head) single(bf16_lo(raw_h), kHeadIter);
+      while (it + 2 <= n_full) {
+        request(wb, it + 1);
+        reduce_iter(wa, std::false_type{});
+        request(wa, it + 1);
+        reduce_iter(wb, std::false_type{});
       }
-    }
-    for (; base < u1; base += per_iter, ++it) {
-      float x[kU][8];
+      while (it < n) {        // at most one whole iteration and one partial one, in one body
+        request(wb, it + 1);
+        reduce_iter(wa, std::true_type{});
 #pragma unroll
-      for (int j = 0; j < kU; ++j) {
-        const int64_t unit = base + j * kT + tid;
-        if (unit < u1) {
-          load_unit<VEC>(rowp, unit, c1, x[j]);
-        } else {
+        for (int j = 0; j < kU; ++j) wa[j] = wb[j];
+      }
+      if (tid < tail) single(bf16_lo(raw_t), kTailIter);
+    } else {
+      for (int64_t base = u0; base < u1; base += per_iter, ++it) {
+        float x[kU][8];
 #pragma unroll
-          for (int k = 0; k < 8; ++k) x[j][k] = -INFINITY;
+        for (int j = 0; j < kU; ++j) {
+          const int64_t unit = base + j * kT + tid;
+          if (unit < u1) {
+            load_unit<VEC>(grid, unit, c1, x[j]);
+          } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x[j][k] = -INFINITY;
+          }
         }
+        accumulate(x, clamp);
       }
-      accumulate(x, clamp);
     }
   };
   pass(std::false_type{});
@@ -328,16 +423,18 @@ __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
   // (the other threads read nothing more, so the re-read costs a few cache
   // lines per chunk instead of one per thread).
   int32_t idx = INT32_MAX;
-  if (m != -INFINITY && m_own == m) {
+  if (m != -INFINITY && m_own == m && it_max < -1) {
+    idx = static_cast<int32_t>(it_max == kHeadIter ? tid : tail0 + tid);
+  } else if (m != -INFINITY && m_own == m) {
     const int64_t base = u0 + static_cast<int64_t>(it_max) * kT * kU;
     for (int j = 0; j < kU && idx == INT32_MAX; ++j) {
       const int64_t unit = base + j * kT + tid;
       if (unit >= u1) break;
       float x[8];
-      load_unit<VEC>(rowp, unit, c1, x);
+      load_unit<VEC>(grid, unit, c1, x);
       for (int k = 0; k < 8; ++k) {
         if (x[k] == m) {
-          idx = static_cast<int32_t>(unit * 8 + k);
+          idx = static_cast<int32_t>(unit * 8 + k - off);
           break;
         }
       }
