@@ -446,6 +446,72 @@ __global__ __launch_bounds__(kT, 1) void window_attention_kernel(AttnParams p) {
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) any_valid |= valid[qb];
   if (p.block_flags && !wg_any(any_valid)) return;
+  // tiles of this split's key range [kb, ke) that any row of the workgroup sees
+  auto tiles_to = [&](int ke) {
+    int kend = ke;
+    if (MODE == 1) {
+      const int r_last = min(M, row0 + kRowsPerTile) - 1;
+      const int i_last = r_last / G;
+      kend = min(ke, P + (i_last / p.block_size + 1) * p.block_size);
+    }
+    return kend > kb ? (kend - kb + kKeyTile - 1) / kKeyTile : 0;
+  };
+
+  // A wave whose 32 rows are all padding (past the window's rows, or of
+  // unflagged blocks) loads its share of every tile and meets the other waves
+  // at their barriers, but computes nothing, so that the wave on the same SIMD
+  // has the matrix cores to itself.  Its path is apart from the others' and
+  // ends here: joined again it would cost them registers (190-300 bytes of
+  // scratch), as it does in the pipelined kernels, which compute their padding.
+  // 8 x 4096 keys, 3 blocks of 32 with 4 query heads per KV head (384 rows in
+  // two tiles of 256): 53.7 -> 51.8 us; 16 x 4000, 2 blocks, 1 query head per
+  // KV head (64 rows of 128): 56.1 -> 54.5 us; full tiles unchanged.
+  if (!PIPE && __builtin_amdgcn_ballot_w64(any_valid) == 0) {
+    const int ntiles = tiles_to(min(n_all, kb + p.kv_chunk));
+    uint32_t koff[Tile<D>::kWaveLoads], voff;
+    k_load_offsets<D>(koff, wpart);
+    if constexpr (VT) voff = vt_load_offset<D>();
+    else voff = (lane >> 1) * 32 + (v_half(lane >> 1, lane & 1) << 4);
+    auto buf = [&](int t) -> char * {
+      const int i = t & 3;
+      return i == 0 ? lds0 : i == 1 ? lds1 : i == 2 ? lds2 : lds3;
+    };
+    // one pass over the tiles: the same requests, waits and barriers as below
+    auto pass = [&]() {
+      int pid = pid0;
+      auto request = [&](int t) {
+        load_tile<D, VT>(p, g, wpage, wpart, pid, koff, voff, buf(t));
+        pid = wave_page(p, b, kb + (t + 1) * kKeyTile, wpage);
+      };
+      auto land = [&](int t, int in_flight) {     // tile t
+        constexpr int per = 2 * Tile<D>::kWaveLoads;
+        if (in_flight >= 2) __builtin_amdgcn_s_waitcnt(wait_vmcnt(2 * per));
+        else if (in_flight == 1) __builtin_amdgcn_s_waitcnt(wait_vmcnt(per));
+        else __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));
+        lds_barrier();
+        const int key0 = kb + t * kKeyTile;
+        if (key0 + kKeyTile > n_all) {
+          zero_v_tail<D, VT>(buf(t), n_all - key0);
+          lds_barrier();
+        }
+      };
+      for (int t = 0; t < 3 && t < ntiles; ++t) request(t);
+      land(0, min(2, ntiles - 1));
+      for (int t = 0; t < ntiles; ++t) {
+        if (t + 3 < ntiles) request(t + 3);
+        if (t + 1 < ntiles) land(t + 1, min(2, ntiles - 2 - t));
+      }
+      lds_barrier();
+    };
+    if (ntiles > 0) pass();
+    if (wg_any(false)) {      // the rerun: the row maxima, then everything again
+      pass();
+      pass();
+    }
+    if constexpr (KS == 2) lds_barrier();   // the hand-over of the second key blocks
+    return;
+  }
+
   constexpr int KK = D / 16;
   bf16x8 qreg[QB][KK];
 #pragma unroll
@@ -470,14 +536,7 @@ __global__ __launch_bounds__(kT, 1) void window_attention_kernel(AttnParams p) {
     }
     lim[qb] = valid[qb] ? min(n, ke) : ke;
   }
-  // keys any row of this workgroup can see
-  int kend = ke;
-  if (MODE == 1) {
-    const int r_last = min(M, row0 + kRowsPerTile) - 1;
-    const int i_last = r_last / G;
-    kend = min(ke, P + (i_last / p.block_size + 1) * p.block_size);
-  }
-  const int ntiles = kend > kb ? (kend - kb + kKeyTile - 1) / kKeyTile : 0;
+  const int ntiles = tiles_to(ke);
 
   // ---- loop-invariant LDS operand offsets of this lane
   constexpr int DB = D / 32;
