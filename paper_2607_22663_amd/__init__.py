@@ -55,9 +55,10 @@ def v_layout_of(k_pages, v_pages):
     """V_TOKEN_MAJOR when v_pages is [num_pages, Hkv, 16, D] like k_pages,
     V_TOKEN_MINOR when it is [num_pages, Hkv, D, 16] (head_dim is never 16)."""
     n_pages, hkv, page, d = k_pages.shape
-    if tuple(v_pages.shape) == (n_pages, hkv, page, d):
+    shape = v_pages.shape
+    if shape == (n_pages, hkv, page, d):
         return V_TOKEN_MAJOR
-    if tuple(v_pages.shape) == (n_pages, hkv, d, page):
+    if shape == (n_pages, hkv, d, page):
         return V_TOKEN_MINOR
     raise ValueError(f"v_pages must be [num_pages, Hkv, 16, D] or [num_pages, Hkv, D, 16] = "
                      f"{(n_pages, hkv, page, d)} or {(n_pages, hkv, d, page)}, got {tuple(v_pages.shape)}")
@@ -86,6 +87,8 @@ _lock = threading.Lock()
 def load(path: Optional[str] = None) -> ctypes.CDLL:
     """Loads libmbe.so (once).  Raises if it is missing or lacks a symbol."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is not None:
             return _lib
@@ -145,11 +148,26 @@ def _on_device(fn):
     @functools.wraps(fn)
     def wrapper(*args, **kwargs):
         t = args[0] if args else None
-        if isinstance(t, torch.Tensor) and t.is_cuda and t.device.index != torch.cuda.current_device():
+        if isinstance(t, torch.Tensor) and t.is_cuda and t.get_device() != _current_device():
             with torch.cuda.device(t.device):
                 return fn(*args, **kwargs)
         return fn(*args, **kwargs)
     return wrapper
+
+
+def _current_device():
+    # (a device tensor exists, so the runtime is initialised)
+    return torch._C._cuda_getDevice()
+
+
+def _raw_stream(device) -> int:
+    """The current stream of the device, as a hipStream_t, without building
+    torch's Stream object (every call asks for it).  Anything but a GPU is left
+    to torch to refuse."""
+    index = device.index
+    if index is None or device.type != "cuda":
+        return torch.cuda.current_stream(device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(index)
 
 
 def _check(call, status):
@@ -158,10 +176,20 @@ def _check(call, status):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_BF16, _I32, _F32 = torch.bfloat16, torch.int32, torch.float32
 
 
 def _need(t: torch.Tensor, name: str, dtype, device, ndim=None):
+    # the usual case in one test; the checks below it say what is wrong
+    try:
+        if (t.dtype is dtype and t.is_contiguous() and t.device == device and (ndim is None or t.dim() == ndim)
+                and isinstance(t, torch.Tensor)):
+            return
+    except AttributeError:
+        pass
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
@@ -183,7 +211,7 @@ def _workspace(kind: str, device: torch.device, nbytes: int) -> Optional[torch.T
     calls on different streams get different buffers and never race."""
     if nbytes == 0:
         return None
-    key = (kind, device.index, torch.cuda.current_stream(device).cuda_stream)
+    key = (kind, device.index, _raw_stream(device))
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
         ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
@@ -205,7 +233,7 @@ def _call_with_workspace(call, size, opts, device, workspace):
             raise ValueError("workspace must be a uint8 device tensor")
         opts.workspace, opts.workspace_bytes = _ptr(workspace), workspace.numel()
         return call()
-    key = ("attn", device.index, torch.cuda.current_stream(device).cuda_stream)
+    key = ("attn", device.index, opts.stream or 0)
     ws = _workspaces.get(key)
     opts.workspace, opts.workspace_bytes = (_ptr(ws), ws.numel()) if ws is not None else (None, 0)
     status = call()
@@ -272,31 +300,52 @@ def window_attention_plan(num_q_heads, k_pages, v_pages, page_table, batch, tota
     return d
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream(device) -> int:
+    return _raw_stream(device)
 
 
 def _attn_common(q, k_pages, v_pages, page_table, prefix_lens, out):
-    dev = q.device
-    _need(q, "q", torch.bfloat16, dev, 3)
-    _need(k_pages, "k_pages", torch.bfloat16, dev, 4)
-    _need(v_pages, "v_pages", torch.bfloat16, dev, 4)
-    _need(page_table, "page_table", torch.int32, dev, 2)
-    _need(prefix_lens, "prefix_lens", torch.int32, dev, 1)
-    n_pages, hkv, page, d = k_pages.shape
+    try:      # the usual case: everything as it should be, in one test
+        index = q.get_device()
+        qs, ts = q.shape, page_table.shape
+        n_pages, hkv, page, d = k_pages.shape
+        usual = (index >= 0 and q.dtype is _BF16 and k_pages.dtype is _BF16 and v_pages.dtype is _BF16
+                 and page_table.dtype is _I32 and prefix_lens.dtype is _I32
+                 and k_pages.get_device() == index and v_pages.get_device() == index
+                 and page_table.get_device() == index and prefix_lens.get_device() == index
+                 and q.is_contiguous() and k_pages.is_contiguous() and v_pages.is_contiguous()
+                 and page_table.is_contiguous() and prefix_lens.is_contiguous()
+                 and len(qs) == 3 and len(ts) == 2 and prefix_lens.shape == (ts[0],) and qs[2] == d
+                 and (out is None or (out.shape == qs and out.dtype is _BF16 and out.get_device() == index
+                                      and out.is_contiguous())))
+    except (AttributeError, ValueError):
+        usual = False
+    if not usual:
+        _attn_explain(q, k_pages, v_pages, page_table, prefix_lens, out)
+        n_pages, hkv, page, d = k_pages.shape
     layout = v_layout_of(k_pages, v_pages)
-    if q.shape[2] != d:
-        raise ValueError(f"q head_dim {q.shape[2]} != cache head_dim {d}")
-    if page_table.shape[0] != prefix_lens.shape[0]:
-        raise ValueError("page_table and prefix_lens disagree on the batch size")
     if out is None:
         out = torch.empty_like(q)
-    else:
-        _need(out, "out", torch.bfloat16, dev, 3)
+    return PagedKV(k_pages.data_ptr(), v_pages.data_ptr(), n_pages, page, hkv, d, layout), out
+
+
+def _attn_explain(q, k_pages, v_pages, page_table, prefix_lens, out):
+    """The checks of _attn_common one by one: raises for the first that fails."""
+    dev = q.device
+    _need(q, "q", _BF16, dev, 3)
+    _need(k_pages, "k_pages", _BF16, dev, 4)
+    _need(v_pages, "v_pages", _BF16, dev, 4)
+    _need(page_table, "page_table", _I32, dev, 2)
+    _need(prefix_lens, "prefix_lens", _I32, dev, 1)
+    v_layout_of(k_pages, v_pages)
+    if q.shape[2] != k_pages.shape[3]:
+        raise ValueError(f"q head_dim {q.shape[2]} != cache head_dim {k_pages.shape[3]}")
+    if page_table.shape[0] != prefix_lens.shape[0]:
+        raise ValueError("page_table and prefix_lens disagree on the batch size")
+    if out is not None:
+        _need(out, "out", _BF16, dev, 3)
         if out.shape != q.shape:
             raise ValueError("out must have the shape of q")
-    kv = PagedKV(_ptr(k_pages), _ptr(v_pages), n_pages, page, hkv, d, layout)
-    return kv, out
 
 
 def _flags_gate(block_flags, shape, gate, device):
@@ -314,6 +363,9 @@ def _host_i32(x, batch, name):
     """A contiguous host int32 copy (kept alive by the caller) or None."""
     if x is None:
         return None
+    if isinstance(x, torch.Tensor) and x.dtype is torch.int32 and not x.is_cuda and x.is_contiguous() and \
+            x.numel() == batch and x.device.type == "cpu":
+        return x
     a = torch.as_tensor(x, dtype=torch.int32, device="cpu").contiguous()
     if a.numel() != batch:
         raise ValueError(f"{name} must have {batch} entries")
