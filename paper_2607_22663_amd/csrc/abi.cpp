@@ -552,12 +552,12 @@ mbe_status run_attention(const void *q, const mbe_paged_kv *kv, const int32_t *p
 
 namespace mbe {
 
-void edit_select_plan(int64_t rows, int64_t vocab, int32_t *chunks, int64_t *chunk_len) {
+void row_plan(int64_t rows, int64_t vocab, int32_t *chunks, int64_t *chunk_len) {
   // Enough workgroups to cover the 256 CUs twice; a chunk keeps at least 4096
   // elements, one full iteration of the workgroup.  (Measured on 64 rows of
   // 131072: 512 workgroups of 4 iterations beat 2048 of one, whose time is
   // dispatch and one memory round trip.)
-  const int64_t target_wgs = 512;
+  const int64_t target_wgs = kEsTargetWgs;
   int64_t c = 1;
   if (rows < target_wgs) {
     c = (target_wgs + rows - 1) / rows;
@@ -572,6 +572,20 @@ void edit_select_plan(int64_t rows, int64_t vocab, int32_t *chunks, int64_t *chu
   if (c < 1) c = 1;
   *chunks = static_cast<int32_t>(c);
   *chunk_len = len;
+}
+
+void edit_select_plan(int64_t rows, int64_t vocab, int32_t *chunks, int64_t *chunk_len) {
+  row_plan(rows, vocab, chunks, chunk_len);
+  // One workgroup per row where cutting rows saves less than its merge launch
+  // costs (4 us): a workgroup alone on its CU reduces about 31 KB/us (its
+  // CU's VALU), all of them together at most 5.5 MB/us, so while
+  //   2 vocab / 31e3 <= 4 + rows * 2 vocab / 5.5e6   (us).
+  // Measured, cut + merge against whole rows: 256 x 131072 20.6 / 16.5 us, 128
+  // x 131072 15.9 / 14.1, 64 x 131072 12.3 / 12.8, 64 x 32000 10.4 / 8.4.
+  if (*chunks > 1 && vocab * (177 - rows) <= 177 * 62000) {
+    *chunks = 1;
+    *chunk_len = (vocab + 7) / 8 * 8;
+  }
 }
 
 mbe_status report(mbe_status s, const char *fmt, ...) {
@@ -609,7 +623,7 @@ mbe_status threshold_update_check(const void *logits, int64_t rows, int64_t voca
     return fail(MBE_ERR_NULL_ARG, "logits, cur_tokens, new_tokens, conf, action and block_changed must be non-NULL");
   int32_t chunks;
   int64_t len;
-  edit_select_plan(rows, vocab, &chunks, &len);
+  row_plan(rows, vocab, &chunks, &len);
   if (rows * chunks > 0x7fffffffLL) return fail(MBE_ERR_BAD_SHAPE, "too many rows");
   *need = mbe_threshold_update_workspace_size(rows, vocab);
   return MBE_OK;
@@ -622,7 +636,7 @@ mbe_status threshold_update_launch(const void *logits, int64_t rows, int64_t voc
                                    const int32_t *run_if_nonzero, void *workspace, void *stream) {
   int32_t chunks;
   int64_t len;
-  edit_select_plan(rows, vocab, &chunks, &len);
+  row_plan(rows, vocab, &chunks, &len);
   EsParams p{};
   p.logits = static_cast<const uint16_t *>(logits);
   p.rows = rows;
@@ -764,7 +778,10 @@ mbe_status mbe_edit_select(const void *logits, int64_t rows, int64_t vocab, int6
 size_t mbe_threshold_update_workspace_size(int64_t rows, int64_t vocab) {
   if (rows < 0 || vocab < 0) return static_cast<size_t>(-1);
   if (rows == 0) return 0;
-  const size_t partials = mbe_edit_select_workspace_size(rows, vocab);
+  int32_t chunks;
+  int64_t len;
+  mbe::row_plan(rows, vocab, &chunks, &len);
+  const size_t partials = chunks > 1 ? align_up(static_cast<size_t>(rows) * chunks * sizeof(mbe::EsPartial)) : 0;
   return align_up(static_cast<size_t>(rows) * sizeof(int32_t)) + partials;   // predictions, then partials
 }
 

@@ -36,8 +36,10 @@
 // packed behind each other, with entropy, 276.7 -> 48.4 us; and an iteration
 // that is not whole no longer sends the chunk through a second pass: 1024 x
 // 32000 39.8 -> 34.2 us.
-// Rows split over several workgroups (few rows) write partials that a small
-// finalize kernel merges in chunk order, so results are bitwise reproducible.
+// Rows split over several workgroups (few rows) write partials that are merged
+// in a fixed order by the next kernel (a small one of their own for edit
+// selection, the per-block step for the update), so results are bitwise
+// reproducible.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -56,7 +58,6 @@ typedef const __attribute__((address_space(1))) uint16_t g_bf16;
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kU = kEsVecPerThread;
-constexpr int kT = kEsThreads;
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
@@ -212,7 +213,7 @@ __device__ __forceinline__ void decide(const EsParams &p, int64_t row, float m, 
   p.changed[row] = change ? 1 : 0;
 }
 
-template <bool VEC, bool ENT>
+template <bool VEC, bool ENT, int kT>
 __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
   __shared__ float sh_m[kT / 64];
   __shared__ float sh_s[kT / 64];
@@ -455,24 +456,23 @@ __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
   decide<ENT>(p, row, m, s, t, idx);
 }
 
-// Rows reduced in several chunks: one wave per row merges the chunk partials
-// (the kernel boundary makes them visible).  Lane l merges chunks l, l + 64,
-// ... in order, then a butterfly combines the lanes; every step is a fixed,
-// commutative merge, so the result is the same on every lane and in every run.
+// Rows reduced in several chunks: the lanes of a group of L (a power of two
+// that holds the chunks, at most 64) merge the chunk partials of one row (the
+// kernel boundary makes them visible).  Lane l merges chunks l, l + L, ... in
+// order, then a butterfly combines the lanes; every step is a fixed,
+// commutative merge, so the result is the same on every lane and in every
+// run (and for every L that holds the chunks: merging with an empty partial
+// changes no bit).
 template <bool ENT>
-__global__ __launch_bounds__(256) void edit_select_finalize_kernel(EsParams p) {
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (row >= p.rows || (p.gate && *p.gate == 0)) return;
-  const int lane = threadIdx.x & 63;
+__device__ __forceinline__ void merge_chunks(const EsParams &p, int64_t row, int lane, int L) {
   const EsPartial *pp = p.partials + row * p.chunks;
   float m = -INFINITY, s = 0.f, t = 0.f;
   int32_t idx = INT32_MAX;
-  for (int c = lane; c < p.chunks; c += 64) {
+  for (int c = lane; c < p.chunks; c += L) {
     const EsPartial q = pp[c];
     merge<ENT>(m, s, t, idx, q.m, q.s, q.t, q.idx);
   }
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
+  for (int o = 1; o < L; o <<= 1) {
     const float m2 = __shfl_xor(m, o);
     const float s2 = __shfl_xor(s, o);
     const float t2 = ENT ? __shfl_xor(t, o) : 0.f;
@@ -482,11 +482,21 @@ __global__ __launch_bounds__(256) void edit_select_finalize_kernel(EsParams p) {
   if (lane == 0) decide<ENT>(p, row, m, s, t, idx);
 }
 
+// Edit selection of rows in several chunks: one wave per row.
+__global__ __launch_bounds__(256) void edit_select_finalize_kernel(EsParams p) {
+  const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  if (row < p.rows) merge_chunks<false>(p, row, threadIdx.x & 63, 64);
+}
+
 // Threshold update, second step: one workgroup per block of block_size rows
 // applies the mask-to-token set, the force-unmask and the token-to-token set
 // to the rows' predictions and confidences.  Each row's current token is read
 // and its new token written by the same thread, so new_tokens may be
-// cur_tokens itself (an in-place update).
+// cur_tokens itself (an in-place update).  Rows reduced in several chunks are
+// merged here first: they have no launch of their own (a launch of a few
+// workgroups is 4 us, the merge well under one: 64 x 131072 with entropy
+// 29.6 -> 25.6 us with the calls around it).
+template <bool ENT>
 __global__ __launch_bounds__(256) void threshold_block_kernel(EsParams p) {
   __shared__ unsigned long long sh_best;
   __shared__ int32_t sh_changed;
@@ -505,7 +515,12 @@ __global__ __launch_bounds__(256) void threshold_block_kernel(EsParams p) {
     sh_best = 0;
     sh_changed = 0;
   }
-  __syncthreads();
+  if (p.chunks > 1) {
+    int L = 2;
+    while (L < p.chunks && L < 64) L <<= 1;
+    for (int i = tid / L; i < p.block_size; i += 256 / L) merge_chunks<ENT>(p, r0 + i, tid % L, L);
+  }
+  __syncthreads();      // (the rows' results are read below by other threads of this workgroup)
   bool any_gamma = false, any_masked = false;
   for (int i = tid; i < p.block_size; i += 256) {
     const int64_t r = r0 + i;
@@ -554,26 +569,37 @@ __global__ __launch_bounds__(256) void threshold_block_kernel(EsParams p) {
 template <bool ENT>
 hipError_t launch_rows(const EsParams &p, bool vector_loads, hipStream_t stream) {
   const dim3 grid(static_cast<unsigned>(p.rows * p.chunks));
-  if (vector_loads)
-    hipLaunchKernelGGL((edit_select_kernel<true, ENT>), grid, dim3(kT), 0, stream, p);
-  else
-    hipLaunchKernelGGL((edit_select_kernel<false, ENT>), grid, dim3(kT), 0, stream, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || p.chunks == 1) return e;
-  hipLaunchKernelGGL(edit_select_finalize_kernel<ENT>, dim3(static_cast<unsigned>((p.rows + 3) / 4)), dim3(256), 0,
-                     stream, p);
+  // Few rows, each by one workgroup: twice the threads, since a workgroup then
+  // has its CU to itself or nearly (256 x 131072: 16.5 us for the call, 18.7
+  // with four times the threads or with four loads per thread; from 512 rows
+  // on the smaller workgroups are better, 24.8 against 28.0 us).
+  if (p.chunks == 1 && p.rows < kEsTargetWgs) {
+    if (vector_loads)
+      hipLaunchKernelGGL((edit_select_kernel<true, ENT, 2 * kEsThreads>), grid, dim3(2 * kEsThreads), 0, stream, p);
+    else
+      hipLaunchKernelGGL((edit_select_kernel<false, ENT, 2 * kEsThreads>), grid, dim3(2 * kEsThreads), 0, stream, p);
+  } else if (vector_loads) {
+    hipLaunchKernelGGL((edit_select_kernel<true, ENT, kEsThreads>), grid, dim3(kEsThreads), 0, stream, p);
+  } else {
+    hipLaunchKernelGGL((edit_select_kernel<false, ENT, kEsThreads>), grid, dim3(kEsThreads), 0, stream, p);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_edit_select(const EsParams &p, bool vector_loads, hipStream_t stream) {
-  return launch_rows<false>(p, vector_loads, stream);
+  const hipError_t e = launch_rows<false>(p, vector_loads, stream);
+  if (e != hipSuccess || p.chunks == 1) return e;
+  hipLaunchKernelGGL(edit_select_finalize_kernel, dim3(static_cast<unsigned>((p.rows + 3) / 4)), dim3(256), 0, stream, p);
+  return hipGetLastError();
 }
 
 hipError_t launch_threshold_update(const EsParams &p, bool vector_loads, hipStream_t stream) {
-  hipError_t e = p.entropy ? launch_rows<true>(p, vector_loads, stream) : launch_rows<false>(p, vector_loads, stream);
+  const hipError_t e =
+      p.entropy ? launch_rows<true>(p, vector_loads, stream) : launch_rows<false>(p, vector_loads, stream);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(threshold_block_kernel, dim3(static_cast<unsigned>(p.rows / p.block_size)), dim3(256), 0, stream,
-                     p);
+  const dim3 grid(static_cast<unsigned>(p.rows / p.block_size));
+  if (p.entropy) hipLaunchKernelGGL(threshold_block_kernel<true>, grid, dim3(256), 0, stream, p);
+  else hipLaunchKernelGGL(threshold_block_kernel<false>, grid, dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 

@@ -64,6 +64,7 @@ hipError_t launch_window_attention(const AttnParams &p, int head_dim, int mask_m
 
 // ------------------------------------------------------------ edit selection
 constexpr int kEsThreads = 256;
+constexpr int64_t kEsTargetWgs = 512; // workgroups that rows are cut into chunks to reach: two per CU
 constexpr int kEsVecPerThread = 2;   // 16-byte loads per thread per iteration
 
 struct EsPartial {
@@ -97,6 +98,9 @@ struct EsParams {
   const int32_t *gate;      // threshold update: when *gate == 0 the pass changes nothing
 };
 
+// Chunks per row of the update (its per-block step merges them), and of edit
+// selection (chunks take a launch of their own there).
+void row_plan(int64_t rows, int64_t vocab, int32_t *chunks, int64_t *chunk_len);
 void edit_select_plan(int64_t rows, int64_t vocab, int32_t *chunks, int64_t *chunk_len);
 hipError_t launch_edit_select(const EsParams &p, bool vector_loads, hipStream_t stream);
 hipError_t launch_threshold_update(const EsParams &p, bool vector_loads, hipStream_t stream);

@@ -1,0 +1,72 @@
+"""Edit selection and the update on both sides of their launch rules: rows
+cut into chunks or not (the vocabulary where the rule turns, for several row
+counts), 512 threads per row below 512 rows and 256 from there, and the update's
+merge of 1 to 64+ chunks per row inside its per-block step, for blocks of one
+row, of a ragged size and of all rows; against the oracle, in-place tokens
+included.  A subset of the rows is compared where the oracle would be slow."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _logits(rows, vocab, seed):
+    g = torch.Generator(DEV).manual_seed(seed)
+    x = torch.empty(rows, vocab, dtype=torch.bfloat16, device=DEV).normal_(0.0, 3.0, generator=g)
+    col = torch.randint(0, vocab, (rows,), generator=g, device=DEV)
+    x[torch.arange(rows, device=DEV), col] = 16.0           # exact in bf16, above every other
+    # some rows tied with an earlier column (another chunk)
+    tie = torch.arange(0, rows, 3, device=DEV)
+    x[tie, col[tie] // 2] = 16.0
+    cur = torch.randint(0, vocab, (rows,), generator=g, device=DEV, dtype=torch.int32)
+    return x, cur
+
+
+# (rows, vocab): 62350 / 97125 / 224025 are where the rule turns at 1, 64 and 128 rows
+@pytest.mark.parametrize("rows,vocab", [(1, 62352), (1, 62353), (1, 4096), (1, 4097), (64, 97119), (64, 97123), (128, 131072),
+                                        (176, 131072), (177, 131073), (511, 20000), (512, 20000), (513, 8191), (3, 200003)])
+def test_edit_select_plans(gpu, rows, vocab):
+    x, cur = _logits(rows, vocab, rows + vocab)
+    n, c, ch = gpu.edit_select(x, cur, 0.5)
+    torch.cuda.synchronize()
+    pick = np.unique(np.linspace(0, rows - 1, min(rows, 24)).astype(int))
+    rn, rc, rch = oracle.edit_select(x[pick].cpu(), cur[pick].cpu(), 0.5)
+    assert np.array_equal(n[pick].cpu().numpy(), rn) and np.array_equal(ch[pick].cpu().numpy(), rch)
+    assert np.max(np.abs(c[pick].cpu().numpy() - rc) / rc) <= 1e-6
+
+
+@pytest.mark.parametrize("rows,vocab,block", [(1, 300000, 1), (2, 131072, 2), (7, 262144, 7), (30, 65537, 10), (96, 131072, 96),
+                                              (256, 131072, 256), (500, 16384, 250), (512, 16384, 512), (48, 9000, 3)])
+@pytest.mark.parametrize("entropy", [True, False])
+def test_update_merges_chunks(gpu, rows, vocab, block, entropy):
+    x, cur = _logits(rows, vocab, rows * 7 + vocab)
+    cur[torch.arange(0, rows, 2, device=DEV)] = vocab         # masked rows
+    ref = None
+    if rows * vocab <= 20_000_000:
+        ref = oracle.threshold_update(x.cpu(), cur.cpu(), vocab, block, 0.5, 0.0, with_entropy=entropy)
+    out = gpu.threshold_update(x, cur, vocab, block, 0.5, 0.0, with_entropy=entropy)
+    tokens = cur.clone()
+    same = {k: torch.empty_like(v) for k, v in out.items()}
+    same["new_tokens"] = tokens                               # in place
+    gpu.threshold_update(x, tokens, vocab, block, 0.5, 0.0, out=same)
+    torch.cuda.synchronize()
+    for k in out:
+        assert torch.equal(out[k], same[k]), f"{k}: in place differs"
+    if ref is None:
+        pick = np.unique(np.linspace(0, rows - 1, 12).astype(int))
+        p, c = oracle.update.prediction(x[pick].cpu())
+        got = out["new_tokens"][pick].cpu().numpy()
+        act = out["action"][pick].cpu().numpy()
+        assert np.array_equal(got[act != 0], p[act != 0])
+        assert np.max(np.abs(out["conf"][pick].cpu().numpy() - c) / c) <= 1e-6
+        return
+    for k in ("new_tokens", "action", "block_changed"):
+        assert np.array_equal(out[k].cpu().numpy().astype(np.int64), np.asarray(ref[k]).astype(np.int64)), k
+    assert int(out["changed_count"][0]) == ref["changed_count"]
+    assert np.max(np.abs(out["conf"].cpu().numpy() - ref["conf"]) / ref["conf"]) <= 1e-6
+    if entropy:
+        assert np.max(np.abs(out["entropy"].cpu().numpy() - ref["entropy"])) <= 1e-5
