@@ -281,7 +281,8 @@ def window_attention_plan(num_q_heads, k_pages, v_pages, page_table, batch, tota
     """The launch plan a window_attention call with these shapes makes (host
     only): dict of splits, kv_chunk, key_split, pipelined, workgroups, and the
     main kernel's name as rocprofv3 reports it (window_attention_kernel<D,
-    MODE, KS, VT, PIPE>)."""
+    MODE, KS, VT, PIPE>, or window_attention_short_kernel<D, MODE, VT, TILES>
+    for 128-row tiles in units of at most 256 keys)."""
     lib = load()
     layout = v_layout_of(k_pages, v_pages)
     kv = PagedKV(None, None, k_pages.shape[0], k_pages.shape[2], k_pages.shape[1], k_pages.shape[3], layout)
@@ -295,6 +296,10 @@ def window_attention_plan(num_q_heads, k_pages, v_pages, page_table, batch, tota
     _check("mbe_window_attention_plan", lib.mbe_window_attention_plan(ctypes.byref(kv), ctypes.byref(opts),
                                                                       ctypes.byref(plan)))
     d = {f: getattr(plan, f) for f, _ in AttnPlan._fields_}
+    if plan.key_split == 2 and plan.kv_chunk <= 256 and os.environ.get("MBE_ATTN_PIPELINE", "")[:1] not in ("0", "1"):
+        d["kernel"] = (f"window_attention_short_kernel<{k_pages.shape[3]},{mode},{int(layout == V_TOKEN_MAJOR)},"
+                       f"{2 if plan.kv_chunk <= 128 else 4}>")
+        return d
     d["kernel"] = (f"window_attention_kernel<{k_pages.shape[3]},{mode},{plan.key_split},"
                    f"{int(layout == V_TOKEN_MAJOR)},{plan.pipelined}>")
     return d

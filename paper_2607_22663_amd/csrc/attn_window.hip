@@ -253,14 +253,14 @@ __device__ __forceinline__ void load_tile(const AttnParams &p, int g, int wpage,
 // Zeroes V entries of keys at or past `nvalid` (tile-relative) so that
 // unread page tails (which may hold anything) cannot reach the P.V product.
 template <int D, int VT>
-__device__ __forceinline__ void zero_v_tail(char *buf, int nvalid) {
+__device__ __forceinline__ void zero_v_tail(char *vbuf, int nvalid) {
   if constexpr (VT) {     // token-major: whole key rows [nvalid, 64) of the tile
-    uint4 *vs = reinterpret_cast<uint4 *>(buf + Tile<D>::kKBytes);
+    uint4 *vs = reinterpret_cast<uint4 *>(vbuf);
     constexpr int RC = Tile<D>::kRowChunks;
     for (int i = nvalid * RC + static_cast<int>(threadIdx.x); i < kKeyTile * RC; i += kT) vs[i] = make_uint4(0, 0, 0, 0);
     return;
   }
-  uint16_t *vs = reinterpret_cast<uint16_t *>(buf + Tile<D>::kKBytes);
+  uint16_t *vs = reinterpret_cast<uint16_t *>(vbuf);
   for (int s = threadIdx.x; s < 4 * D; s += kT) {   // row s: page s / D, dim s % D, 16 keys
     const int k0 = (s / D) * kPageSize;
     if (k0 + kPageSize <= nvalid) continue;
@@ -270,6 +270,33 @@ __device__ __forceinline__ void zero_v_tail(char *buf, int nvalid) {
     for (int k = 0; k < kPageSize; ++k)
       if (k0 + k >= nvalid) e[v_half(d, k >> 3) * 8 + (k & 7)] = 0;
   }
+}
+
+// Work unit of this workgroup (false: none), see the order kinds in AttnParams.
+// All indices fit 31 bits (the host bounds the grid), so the divisions are
+// 32-bit: as 64-bit ones they were 150 instructions each, before the first
+// load of the kernel.
+__device__ __forceinline__ bool find_unit(const AttnParams &p, int &split, int &b, int &g, int &qtile) {
+  const uint32_t id = blockIdx.x, qtiles = p.qtiles, hkv = p.num_kv_heads;
+  uint32_t grp;
+  if (p.order_kind == kOrderUnits) {
+    const uint32_t u = p.order[id];             // the grid has order_n workgroups
+    if (u == kNoUnit) return false;
+    grp = u / qtiles;
+    qtile = u - grp * qtiles;
+  } else {
+    const uint32_t slot = id / kXcds, col = slot / qtiles;
+    grp = col * kXcds + id % kXcds;
+    if (grp >= static_cast<uint32_t>(p.groups)) return false;
+    qtile = slot - col * qtiles;
+  }
+  const uint32_t per_split = static_cast<uint32_t>(p.batch) * hkv;
+  split = grp / per_split;
+  const uint32_t rg = grp - split * per_split;
+  const int rank = rg / hkv;
+  g = rg - rank * hkv;
+  b = (p.order_kind == kOrderSeqs && rank < p.order_n) ? p.order[rank] : rank;
+  return true;
 }
 
 // KS = 1: the eight waves own 32 rows each.  KS = 2 (at most 128 rows per
@@ -330,26 +357,8 @@ __global__ __launch_bounds__(kT, 1) void window_attention_kernel(AttnParams p) {
   // gated off: the call does nothing (the gate is read together with the
   // work unit and checked once both are in)
   const int32_t gate = load_now(p.gate ? p.gate : p.prefix_lens);
-  const int64_t id = blockIdx.x;
-  int64_t grp;
-  int qtile;
-  if (p.order_kind == kOrderUnits) {
-    const int u = p.order[id];             // the grid has order_n workgroups
-    if (u == kNoUnit) return;
-    grp = u / p.qtiles;
-    qtile = u % p.qtiles;
-  } else {
-    const int64_t slot = id / kXcds;
-    grp = (slot / p.qtiles) * kXcds + id % kXcds;
-    if (grp >= p.groups) return;
-    qtile = static_cast<int>(slot % p.qtiles);
-  }
-  const int64_t per_split = static_cast<int64_t>(p.batch) * p.num_kv_heads;
-  const int split = static_cast<int>(grp / per_split);
-  const int64_t rg = grp % per_split;
-  const int rank = static_cast<int>(rg / p.num_kv_heads);
-  const int g = static_cast<int>(rg % p.num_kv_heads);
-  const int b = (p.order_kind == kOrderSeqs && rank < p.order_n) ? p.order[rank] : rank;
+  int split, b, g, qtile;
+  if (!find_unit(p, split, b, g, qtile)) return;
   if (p.gate && gate == 0) return;
 
   const int G = p.group;
@@ -491,7 +500,7 @@ __global__ __launch_bounds__(kT, 1) void window_attention_kernel(AttnParams p) {
         lds_barrier();
         const int key0 = kb + t * kKeyTile;
         if (key0 + kKeyTile > n_all) {
-          zero_v_tail<D, VT>(buf(t), n_all - key0);
+          zero_v_tail<D, VT>(buf(t) + Tile<D>::kKBytes, n_all - key0);
           lds_barrier();
         }
       };
@@ -735,7 +744,7 @@ __global__ __launch_bounds__(kT, 1) void window_attention_kernel(AttnParams p) {
   auto fix_tail = [&](int t) {
     const int key0 = kb + t * kKeyTile;
     if (key0 + kKeyTile > n_all) {
-      zero_v_tail<D, VT>(buf_of(t), n_all - key0);
+      zero_v_tail<D, VT>(buf_of(t) + Tile<D>::kKBytes, n_all - key0);
       lds_barrier();
     }
   };
@@ -869,7 +878,7 @@ __global__ __launch_bounds__(kT, 1) void window_attention_kernel(AttnParams p) {
   auto fix_tail5 = [&](int t) {
     const int key0 = kb + t * kKeyTile;
     if (key0 + kKeyTile > n_all) {
-      zero_v_tail<D, VT>(buf5(t), n_all - key0);
+      zero_v_tail<D, VT>(buf5(t) + Tile<D>::kKBytes, n_all - key0);
       lds_barrier();
     }
   };
@@ -1115,6 +1124,262 @@ __global__ __launch_bounds__(kT, 1) void window_attention_kernel(AttnParams p) {
   MBE_TL_END();
 }
 
+// Reads every field that the short kernel uses, with one wait: the compiler
+// would read each where it is first used, a dozen dependent trips before the
+// first load.
+__device__ __forceinline__ void read_fields(const AttnParams &p) {
+  asm volatile("" ::"s"(p.gate), "s"(p.prefix_lens), "s"(p.window_lens), "s"(p.page_table), "s"(p.q), "s"(p.k_pages),
+               "s"(p.v_pages), "s"(p.block_flags), "s"(p.order_kind), "s"(p.qtiles), "s"(p.num_kv_heads), "s"(p.batch),
+               "s"(p.group), "s"(p.kv_chunk), "s"(p.fixed_window), "s"(p.max_pages), "s"(p.max_window), "s"(p.max_prefix),
+               "s"(p.splits), "s"(p.total_q), "s"(p.num_q_heads), "s"(p.num_pages), "s"(p.groups));
+}
+
+// The same attention for units of at most NT key tiles (2 or 4) and 128 rows:
+// the smallest calls, whose time is latency, not throughput.  Waves w and
+// w + 4 own the same 32 rows and take the first and the second 32-key block of
+// every tile (as with KS = 2 above).  Differences that the short length allows:
+// every tile of the unit has its own buffer, so all K, Q and V loads are
+// requested at once, right behind the lengths, and waited for twice (K and Q,
+// then V); all scores of a wave are held in registers, so the reference is
+// their true maximum and no sum can overflow (no rerun); and the code is short
+// and straight (10 KB against 36), as each launch fetches it anew.  What bounds
+// it: one round trip for the lengths, one for the loads, the merge's launch.
+// 1 x 2048 keys, 2 blocks of 32, 16 / 4 heads: 22.3 -> 18.8 us a call.
+template <int D, int MODE, int VT, int NT>
+__device__ __forceinline__ void short_unit(const AttnParams &p) {
+  constexpr int KK = D / 16, DB = D / 32, DH = DB / 2;
+  constexpr int PB = Tile<D>::kPageBytes, WL = Tile<D>::kWaveLoads;
+  constexpr int kSlices = kWaves / 2;                          // 32-row slices of the tile
+  constexpr int kGiveBytes = kWaves * DH * 16 * 64 * 4;        // half of every wave's O, handed over at the end
+  constexpr int kKBuf = NT * Tile<D>::kKBytes > kGiveBytes ? NT * Tile<D>::kKBytes : kGiveBytes;
+  __shared__ __align__(1024) char lds_k[kKBuf];
+  __shared__ __align__(1024) char lds_v[NT * Tile<D>::kVBytes];
+  __shared__ float lds_m[kWaves][64], lds_l[kWaves][64];
+
+  read_fields(p);
+  // ---- work unit, as in the general kernel
+  const int32_t gate = load_now(p.gate ? p.gate : p.prefix_lens);
+  int split, b, g, qtile;
+  if (!find_unit(p, split, b, g, qtile)) return;
+  if (p.gate && gate == 0) return;
+
+  const int G = p.group;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = lane & 31, h = lane >> 5;
+  const int wrow = wv % kSlices, kown = wv / kSlices;
+  const int wpage = wv % 4, wpart = wv / 4;
+  const int kb = split * p.kv_chunk;
+
+  // lengths and, in lane 4t + w, the page of tile t that waves w and w + 4 load
+  const bool fixed = p.fixed_window >= 0;
+  const int32_t *wl = fixed ? p.prefix_lens : p.window_lens;
+  const int32_t P_dev = load_now(p.prefix_lens + b);
+  const int32_t W_dev = load_now(wl + b);
+  const int32_t wl_lane = load_now(wl + min(lane, b));
+  const int slot0 = min(kb / kPageSize + (lane & 15), p.max_pages - 1);
+  const int32_t pages = load_now(p.page_table + static_cast<int64_t>(b) * p.max_pages + slot0);
+  const int W = fixed ? p.fixed_window : min(max(W_dev, 0), p.max_window);
+  const int P = min(max(P_dev, 0), p.max_prefix);
+  const int M = G * W;
+  const int row0 = qtile * kShortRows;
+  const int n_all = P + W;
+  const int nsplit = min(p.splits, max(1, (n_all + p.kv_chunk - 1) / p.kv_chunk));
+  if (row0 >= M || split >= nsplit) return;
+
+  int cu = 0;      // first query row of sequence b
+  if (fixed) {
+    cu = b * p.fixed_window;
+  } else {
+    cu = lane < b ? min(max(wl_lane, 0), p.max_window) : 0;
+    for (int j = lane + 64; j < b; j += 64) cu += min(max(p.window_lens[j], 0), p.max_window);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) cu += __shfl_xor(cu, o);
+    cu = __builtin_amdgcn_readfirstlane(cu);
+  }
+  auto row_valid = [&](int r) -> bool {
+    return r < M && cu + r / G < p.total_q &&
+           (!p.block_flags || p.block_flags[static_cast<int64_t>(b) * p.flag_stride + (r / G) / p.block_size]);
+  };
+  // no flagged row in the tile: nothing to do (every wave tests all 128 rows)
+  if (p.block_flags) {
+    const bool any = row_valid(row0 + lane) || row_valid(row0 + 64 + lane);
+    if (__builtin_amdgcn_ballot_w64(any) == 0) return;
+  }
+  const int r = row0 + wrow * 32 + c;          // this lane's row
+  const bool valid = row_valid(r);
+  const int64_t rowidx = static_cast<int64_t>(cu + (valid ? r / G : 0)) * p.num_q_heads + g * G + (valid ? r % G : 0);
+
+  // ---- key range [kb, ke), its tiles that any row of the workgroup sees, and
+  // the keys [kb, seen) that every row sees
+  const int ke = min(n_all, kb + p.kv_chunk);
+  int kend = ke, seen = ke, lim = ke;
+  if (MODE == 1) {
+    kend = min(ke, P + (((min(M, row0 + kShortRows) - 1) / G) / p.block_size + 1) * p.block_size);
+    seen = min(ke, P + ((row0 / G) / p.block_size + 1) * p.block_size);
+    if (valid) lim = min(ke, P + ((r / G) / p.block_size + 1) * p.block_size);
+  }
+  const int ntiles = kend > kb ? min(NT, (kend - kb + kKeyTile - 1) / kKeyTile) : 0;
+
+  // ---- all loads: K of every tile, Q, V of every tile.  Tiles past the last
+  // are requested too (from clamped, readable pages) so that the counts of
+  // loads in flight are constants; nothing reads them.
+  uint32_t kld[WL], vld;
+  k_load_offsets<D>(kld, wpart);
+  if constexpr (VT) vld = vt_load_offset<D>();
+  else vld = (lane >> 1) * 32 + (v_half(lane >> 1, lane & 1) << 4);
+  int64_t page[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int pid = __builtin_amdgcn_readlane(pages, 4 * t + wpage);
+    page[t] = (static_cast<int64_t>(min(max(pid, 0), p.num_pages - 1)) * p.num_kv_heads + g) * PB;
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int j = 0; j < WL; ++j)
+      __builtin_amdgcn_global_load_lds(reinterpret_cast<const char *>(p.k_pages) + page[t] + kld[j],
+                                       (lds_void *)(lds_k + t * Tile<D>::kKBytes + wpage * PB + (wpart * WL + j) * 1024),
+                                       16, 0, kStreamLoad);
+  bf16x8 qreg[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk)
+    qreg[kk] = valid ? *reinterpret_cast<const bf16x8 *>(p.q + rowidx * D + kk * 16 + h * 8) : bf16x8{};
+  asm volatile("" ::: "memory");           // V is requested after all of K
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int j = 0; j < WL; ++j)
+      __builtin_amdgcn_global_load_lds(reinterpret_cast<const char *>(p.v_pages) + page[t] + (wpart * WL + j) * 1024 + vld,
+                                       (lds_void *)(lds_v + t * Tile<D>::kVBytes + wpage * PB + (wpart * WL + j) * 1024),
+                                       16, 0, kStreamLoad);
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(wait_vmcnt(NT * WL));     // K is in LDS
+  lds_barrier();
+
+  // ---- scores of this wave's 32-key block of every tile
+  const int krow = perm_row(c);
+  const bool active = __builtin_amdgcn_ballot_w64(valid) != 0;   // else all 32 rows are padding
+  f32x16 s[NT];
+  float m = kNegInf;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    if (t >= ntiles || !active) continue;
+    const char *kt = lds_k + t * Tile<D>::kKBytes + (krow + 32 * kown) * (2 * D);
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+      s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_read8(kt, ((2 * kk + h) ^ k_swz<D>(krow)) << 4), qreg[kk],
+                                                     kk == 0 ? f32x16{} : s[t], 0, 0, 0);
+    if (kb + (t + 1) * kKeyTile > seen) {
+      const int room = lim - (kb + t * kKeyTile + 32 * kown) - 8 * h;
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (16 * (v >> 3) + (v & 7) >= room) s[t][v] = kNegInf;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) m = fmaxf(m, s[t][v]);
+  }
+  m = fmaxf(m, __shfl_xor(m, 32)) * p.scale_log2;
+  const float msafe = m == kNegInf ? 0.f : m;
+
+  __builtin_amdgcn_s_waitcnt(wait_vmcnt(0));           // V is in LDS
+  lds_barrier();                                       // and every wave is done with K
+  if (kb + ntiles * kKeyTile > n_all) {                // (only the last tile can hold keys past n_all)
+    const int t = ntiles - 1;
+    zero_v_tail<D, VT>(lds_v + t * Tile<D>::kVBytes, n_all - (kb + t * kKeyTile));
+    lds_barrier();
+  }
+
+  // ---- numerators, their bf16 sums, O^T += V^T . P^T
+  f32x16 acc[DB];
+  float l = 0.f;
+#pragma unroll
+  for (int db = 0; db < DB; ++db) acc[db] = f32x16{};
+  const int vrow = 8 * h + ((lane & 15) >> 2);         // token-major V: see the general kernel
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    if (t >= ntiles || !active) continue;
+    float e[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) e[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][v], p.scale_log2, -msafe));
+#pragma unroll
+    for (int mm = 0; mm < 2; ++mm) {
+      const u32x4 w = {pack_bf16x2(e[8 * mm + 0], e[8 * mm + 1]), pack_bf16x2(e[8 * mm + 2], e[8 * mm + 3]),
+                       pack_bf16x2(e[8 * mm + 4], e[8 * mm + 5]), pack_bf16x2(e[8 * mm + 6], e[8 * mm + 7])};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t wk = w[k];
+        l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, wk), kOnes2, l, false);
+      }
+      const char *vt = lds_v + t * Tile<D>::kVBytes + (2 * kown + mm) * PB;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        bf16x8 va;
+        if constexpr (VT) {
+          const int chunk = 4 * db + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+          const char *at = vt + vrow * (2 * D) + ((chunk ^ v_swz<D>(vrow)) << 4) + 8 * (lane & 1);
+          va = __builtin_shufflevector(lds_read_tr4(at), lds_read_tr4(at + 4 * (2 * D)), 0, 1, 2, 3, 4, 5, 6, 7);
+        } else {
+          va = lds_read8(vt, c * (kPageSize * 2) + (v_half(c, h) << 4) + db * 32 * (kPageSize * 2));
+        }
+        acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, __builtin_bit_cast(bf16x8, w), acc[db], 0, 0, 0);
+      }
+    }
+  }
+  l += __shfl_xor(l, 32);
+
+  // ---- the two waves of a row slice exchange halves of O (wave w keeps the
+  // first half of the dims, wave w + 4 the second) and their sums, each
+  // relative to its own maximum, through the K buffers
+  float *give = reinterpret_cast<float *>(lds_k) + wv * (DH * 16 * 64) + lane;
+  const float *take = reinterpret_cast<const float *>(lds_k) + (wv ^ kSlices) * (DH * 16 * 64) + lane;
+#pragma unroll
+  for (int db = 0; db < DH; ++db)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) give[(db * 16 + v) * 64] = kown ? acc[db][v] : acc[DH + db][v];
+  lds_m[wv][lane] = m;
+  lds_l[wv][lane] = l;
+  lds_barrier();
+  if (!valid) return;                                  // no barrier follows
+  const float mo = lds_m[wv ^ kSlices][lane];
+  const float mt = fmaxf(m, mo);
+  const float f = m == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m - mt);
+  const float fo = mo == kNegInf ? 0.f : __builtin_amdgcn_exp2f(mo - mt);
+  const float lt = f * l + fo * lds_l[wv ^ kSlices][lane];
+  auto half_out = [&](float scale, auto store) {       // this wave's half of the dims, four at a time
+#pragma unroll
+    for (int db = 0; db < DH; ++db)
+#pragma unroll
+      for (int gi = 0; gi < 4; ++gi) {
+        float o[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float own = kown ? acc[DH + db][4 * gi + v] : acc[db][4 * gi + v];
+          o[v] = (f * own + fo * take[(db * 16 + 4 * gi + v) * 64]) * scale;
+        }
+        store(kown * (D / 2) + db * 32 + 8 * gi + 4 * h, o);
+      }
+  };
+  if (nsplit == 1) {
+    uint16_t *orow = p.out + rowidx * D;
+    half_out(lt > 0.f ? 1.f / lt : 0.f, [&](int d0, const float (&o)[4]) {
+      *reinterpret_cast<uint2 *>(orow + d0) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
+    });
+    return;
+  }
+  const int64_t part = split * (static_cast<int64_t>(p.total_q) * p.num_q_heads) + rowidx;
+  half_out(1.f, [&](int d0, const float (&o)[4]) {
+    *reinterpret_cast<float4 *>(p.part_o + part * D + d0) = make_float4(o[0], o[1], o[2], o[3]);
+  });
+  if (h == 0 && kown == 0) *reinterpret_cast<float2 *>(p.part_ml + part * 2) = make_float2(mt, lt);
+}
+
+template <int D, int MODE, int VT, int NT>
+__global__ __launch_bounds__(kT, 1) void window_attention_short_kernel(AttnParams p) {
+  short_unit<D, MODE, VT, NT>(p);
+}
+
 // Split-KV merge, run after the main kernel when some sequence was split (the
 // kernel boundary makes every partial result visible; no cross-workgroup
 // fences inside the main kernel).  Block (x, b) merges items x*256 .. of
@@ -1158,9 +1423,11 @@ __global__ __launch_bounds__(256) void window_attention_merge_kernel(AttnParams 
   if (item >= items) return;
   const int64_t r = item / DI;              // (window row, query head) within the sequence
   const int d0 = static_cast<int>(item % DI) * kMergeDims;
-  if (cu + r / p.num_q_heads >= p.total_q) return;
-  if (p.block_flags &&
-      !p.block_flags[static_cast<int64_t>(b) * p.flag_stride + (r / p.num_q_heads) / p.block_size])
+  if (r >= static_cast<int64_t>(p.total_q) * p.num_q_heads) return;
+  // window row (r fits 32 bits, being a row of q; a 64-bit division is 150 instructions)
+  const uint32_t i = static_cast<uint32_t>(r) / static_cast<uint32_t>(p.num_q_heads);
+  if (cu + static_cast<int64_t>(i) >= p.total_q) return;
+  if (p.block_flags && !p.block_flags[static_cast<int64_t>(b) * p.flag_stride + i / static_cast<uint32_t>(p.block_size)])
     return;                                 // row of an unflagged block: not written
   const int64_t rowidx = static_cast<int64_t>(cu) * p.num_q_heads + r;
   const int64_t split_stride = static_cast<int64_t>(p.total_q) * p.num_q_heads;
@@ -1234,7 +1501,15 @@ template <int D, int MODE>
 hipError_t launch_t(const AttnParams &p, hipStream_t stream) {
   const int64_t grid = p.order_kind == kOrderUnits ? p.order_n : p.slots_per_xcd * kXcds;
   const dim3 g(static_cast<unsigned>(grid)), blk(kT);
-  if (p.v_token_major) {
+  if (p.short_tiles) {
+    if (p.v_token_major) {
+      if (p.short_tiles == 2) hipLaunchKernelGGL((window_attention_short_kernel<D, MODE, 1, 2>), g, blk, 0, stream, p);
+      else hipLaunchKernelGGL((window_attention_short_kernel<D, MODE, 1, 4>), g, blk, 0, stream, p);
+    } else {
+      if (p.short_tiles == 2) hipLaunchKernelGGL((window_attention_short_kernel<D, MODE, 0, 2>), g, blk, 0, stream, p);
+      else hipLaunchKernelGGL((window_attention_short_kernel<D, MODE, 0, 4>), g, blk, 0, stream, p);
+    }
+  } else if (p.v_token_major) {
     if (p.key_split == 2) hipLaunchKernelGGL((window_attention_kernel<D, MODE, 2, 1, 0>), g, blk, 0, stream, p);
     else hipLaunchKernelGGL((window_attention_kernel<D, MODE, 1, 1, 0>), g, blk, 0, stream, p);
   } else {

@@ -16,6 +16,8 @@ constexpr int kKeyTile = 64;          // keys per LDS tile (4 pages)
 constexpr int kRowsPerWave = 32;      // packed (window position, q head) rows per wave
 constexpr int kWaves = 8;               // two per SIMD
 constexpr int kRowsPerTile = kRowsPerWave * kWaves;   // rows per workgroup
+constexpr int kShortRows = 128;         // rows per workgroup where two waves share 32 rows
+constexpr int kShortTiles = 4;          // longest unit of the short kernel, in key tiles
 constexpr int kXcds = 8;              // MI355X: workgroups go round-robin over 8 XCDs
 constexpr int kMaxOrder = 1024;       // dispatch-order entries passed in the kernel arguments
 constexpr uint16_t kNoUnit = 0xFFFF;  // dispatch-table slot without work
@@ -40,6 +42,7 @@ struct AttnParams {
   int32_t qtiles, splits, kv_chunk;
   int32_t key_split;          // 1, or 2 when a sequence has at most 128 rows per KV head
   int32_t v_token_major;      // V pages [16][D] (like K) instead of [D][16]
+  int32_t short_tiles;        // 0, or 2 / 4: the kernel for units of at most that many key tiles (128-row tiles)
   int32_t pipelined;          // software-pipelined key loop (token-minor V, no key split)
   int64_t groups;             // (split, sequence rank, KV head) groups of qtiles work units
   int64_t slots_per_xcd;      // grid = kXcds * slots_per_xcd workgroups
