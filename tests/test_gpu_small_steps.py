@@ -1,0 +1,25 @@
+"""The split merge with 1, 2, 4 and 8 lanes per item (split counts on both
+sides of each, ragged so that some sequences have fewer), and the refresh flags
+around their 64 lanes, in place too."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+import test_gpu_attention as A
+from gpu_util import assert_attn_close
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("nsplit", [2, 8, 9, 15, 16, 17, 25, 32, 33, 47, 64, 65, 130])
+@pytest.mark.parametrize("D", [64, 128])
+def test_merge_lanes(gpu, nsplit, D):
+    n = nsplit * 64
+    spec = synth.AttnSpec(3, 16, 2, ("fixed", 0), 6, 2, D)
+    case = synth.make_attention_case(spec, nsplit, prefix_lens=[n - 32, n // 2, 1], window_lens=[32, 16, 32],
+                                     tail_fill=float("nan"), v_token_major=nsplit % 2 == 1)
+    for mode in ("bidir", "block_causal"):
+        out = A.run_case(gpu, case, mode, kv_split_tokens=64)
+        assert_attn_close(out, A.oracle_case(case, mode), f"{nsplit} splits D {D} {mode}")
