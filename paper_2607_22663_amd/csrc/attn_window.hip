@@ -272,33 +272,6 @@ __device__ __forceinline__ void zero_v_tail(char *vbuf, int nvalid) {
   }
 }
 
-// Work unit of this workgroup (false: none), see the order kinds in AttnParams.
-// All indices fit 31 bits (the host bounds the grid), so the divisions are
-// 32-bit: as 64-bit ones they were 150 instructions each, before the first
-// load of the kernel.
-__device__ __forceinline__ bool find_unit(const AttnParams &p, int &split, int &b, int &g, int &qtile) {
-  const uint32_t id = blockIdx.x, qtiles = p.qtiles, hkv = p.num_kv_heads;
-  uint32_t grp;
-  if (p.order_kind == kOrderUnits) {
-    const uint32_t u = p.order[id];             // the grid has order_n workgroups
-    if (u == kNoUnit) return false;
-    grp = u / qtiles;
-    qtile = u - grp * qtiles;
-  } else {
-    const uint32_t slot = id / kXcds, col = slot / qtiles;
-    grp = col * kXcds + id % kXcds;
-    if (grp >= static_cast<uint32_t>(p.groups)) return false;
-    qtile = slot - col * qtiles;
-  }
-  const uint32_t per_split = static_cast<uint32_t>(p.batch) * hkv;
-  split = grp / per_split;
-  const uint32_t rg = grp - split * per_split;
-  const int rank = rg / hkv;
-  g = rg - rank * hkv;
-  b = (p.order_kind == kOrderSeqs && rank < p.order_n) ? p.order[rank] : rank;
-  return true;
-}
-
 // KS = 1: the eight waves own 32 rows each.  KS = 2 (at most 128 rows per
 // sequence and KV head): waves w and w + 4 own the same 32 rows and split the
 // keys, wave w taking the first and wave w + 4 the second 32-key block of
@@ -357,8 +330,26 @@ __global__ __launch_bounds__(kT, 1) void window_attention_kernel(AttnParams p) {
   // gated off: the call does nothing (the gate is read together with the
   // work unit and checked once both are in)
   const int32_t gate = load_now(p.gate ? p.gate : p.prefix_lens);
-  int split, b, g, qtile;
-  if (!find_unit(p, split, b, g, qtile)) return;
+  const int64_t id = blockIdx.x;
+  int64_t grp;
+  int qtile;
+  if (p.order_kind == kOrderUnits) {
+    const int u = p.order[id];             // the grid has order_n workgroups
+    if (u == kNoUnit) return;
+    grp = u / p.qtiles;
+    qtile = u % p.qtiles;
+  } else {
+    const int64_t slot = id / kXcds;
+    grp = (slot / p.qtiles) * kXcds + id % kXcds;
+    if (grp >= p.groups) return;
+    qtile = static_cast<int>(slot % p.qtiles);
+  }
+  const int64_t per_split = static_cast<int64_t>(p.batch) * p.num_kv_heads;
+  const int split = static_cast<int>(grp / per_split);
+  const int64_t rg = grp % per_split;
+  const int rank = static_cast<int>(rg / p.num_kv_heads);
+  const int g = static_cast<int>(rg % p.num_kv_heads);
+  const int b = (p.order_kind == kOrderSeqs && rank < p.order_n) ? p.order[rank] : rank;
   if (p.gate && gate == 0) return;
 
   const int G = p.group;
@@ -1122,6 +1113,34 @@ __global__ __launch_bounds__(kT, 1) void window_attention_kernel(AttnParams p) {
     }
   }
   MBE_TL_END();
+}
+
+// Work unit of this workgroup (false: none), as in the general kernel, but with
+// 32-bit divisions (all indices fit 31 bits, the host bounds the grid): 64-bit
+// ones are 150 instructions each, before the first load of the kernel.  The
+// general kernel gained nothing from them (32 x 512-8192: 102.4 / 102.2 us), and
+// its pipelined form spilled one dword more.
+__device__ __forceinline__ bool find_unit(const AttnParams &p, int &split, int &b, int &g, int &qtile) {
+  const uint32_t id = blockIdx.x, qtiles = p.qtiles, hkv = p.num_kv_heads;
+  uint32_t grp;
+  if (p.order_kind == kOrderUnits) {
+    const uint32_t u = p.order[id];             // the grid has order_n workgroups
+    if (u == kNoUnit) return false;
+    grp = u / qtiles;
+    qtile = u - grp * qtiles;
+  } else {
+    const uint32_t slot = id / kXcds, col = slot / qtiles;
+    grp = col * kXcds + id % kXcds;
+    if (grp >= static_cast<uint32_t>(p.groups)) return false;
+    qtile = slot - col * qtiles;
+  }
+  const uint32_t per_split = static_cast<uint32_t>(p.batch) * hkv;
+  split = grp / per_split;
+  const uint32_t rg = grp - split * per_split;
+  const int rank = rg / hkv;
+  g = rg - rank * hkv;
+  b = (p.order_kind == kOrderSeqs && rank < p.order_n) ? p.order[rank] : rank;
+  return true;
 }
 
 // Reads every field that the short kernel uses, with one wait: the compiler
