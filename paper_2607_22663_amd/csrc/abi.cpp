@@ -588,7 +588,7 @@ void row_plan(int64_t rows, int64_t vocab, int32_t *chunks, int64_t *chunk_len) 
     if (c < 1) c = 1;
   }
   int64_t len = (vocab + c - 1) / c;
-  len = (len + 7) / 8 * 8;
+  len = std::max<int64_t>(8, (len + 7) / 8 * 8);    // (vocab 0 is refused by the calls, not by the size queries)
   c = (vocab + len - 1) / len;
   if (c < 1) c = 1;
   *chunks = static_cast<int32_t>(c);

@@ -1,9 +1,12 @@
 """C ABI checks that need no GPU: the library loads, exports every declared
 symbol, and rejects bad arguments on the host before any HIP call."""
+import ast
 import ctypes
 import math
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -281,6 +284,19 @@ def test_refresh_validation(lib):
     assert lib.mbe_refresh_blocks(_vp(16), 2, 4, 2, _vp(16), None) == 3
     assert lib.mbe_refresh_blocks(None, 2, 4, 0, _vp(16), None) == 1
     assert lib.mbe_refresh_blocks(None, 0, 4, 0, None, None) == 0
+
+
+def test_size_queries_at_vocab_zero():
+    """A vocabulary of 0 is refused by the calls; the size queries, which the
+    binding asks first, answer (a process of its own: a fault in one would end
+    the test run)."""
+    code = ("import paper_2607_22663_amd as m; l = m.load(); "
+            "print([[f(r, 0) for r in (0, 1, 64, 512, 100000)] for f in "
+            "(l.mbe_edit_select_workspace_size, l.mbe_threshold_update_workspace_size)])")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, (r.returncode, r.stderr[-500:])
+    # no partials; the update keeps its predictions, 4 bytes a row in whole 256s
+    assert ast.literal_eval(r.stdout.strip()) == [[0] * 5, [0, 256, 256, 2048, 400128]]
 
 
 def test_header_is_plain_c_and_links(tmp_path):

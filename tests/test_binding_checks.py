@@ -76,3 +76,13 @@ def test_usual_call_runs(gpu):
     out = gpu.window_attention(*a, 32, max_prefix_len=64, max_window_len=32)
     torch.cuda.synchronize()
     assert out.shape == a[0].shape and bool((out == 0).all())
+
+
+@pytest.mark.gpu
+def test_vocab_zero_raises(gpu):
+    logits = torch.zeros(32, 64, dtype=torch.bfloat16, device="cuda:0")
+    cur = torch.zeros(32, dtype=torch.int32, device="cuda:0")
+    with pytest.raises(gpu.MbeError, match="vocab must be >= 1"):
+        gpu.threshold_update(logits, cur, 63, 32, 0.5, 0.0, vocab=0)
+    with pytest.raises(gpu.MbeError, match="vocab must be >= 1"):
+        gpu.edit_select(logits, cur, 0.5, vocab=0)
