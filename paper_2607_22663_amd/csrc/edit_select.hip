@@ -41,6 +41,7 @@
 // selection, the per-block step for the update), so results are bitwise
 // reproducible.
 #include <hip/hip_runtime.h>
+#include <cfloat>
 #include <stdint.h>
 
 #include <type_traits>
@@ -74,10 +75,30 @@ constexpr float kYMin = -256.f;
 // The reference of a running maximum m: m log2(e) rounded to fp32.  All sums
 // are kept relative to it.  The product is formed by its own instruction:
 // fused into a following subtraction (d = ref(m) - ref(M)) it would lose the
-// rounding that the sums were accumulated against.
-__device__ __forceinline__ float ref_of(float m) {
+// rounding that the sums were accumulated against.  Kept finite: for logits
+// near the type's lowest value (rows masked with it instead of -inf) the
+// product overflows, and a thread that had met only such logits would hold an
+// infinite sum, which no later maximum rescales to 0.  Its terms are 0
+// relative to the finite reference.
+__device__ __forceinline__ float ref_raw(float m) {
   float r;
   asm("v_mul_f32 %0, %1, %2" : "=v"(r) : "v"(m), "v"(kLog2e));
+  return r;
+}
+__device__ __forceinline__ float at_least_lowest(float r) {
+  float f;      // (fmaxf would quiet the product first, one more instruction)
+  asm("v_max_f32 %0, %1, %2" : "=v"(f) : "v"(r), "v"(-FLT_MAX));
+  return f;
+}
+__device__ __forceinline__ float ref_of(float m) { return at_least_lowest(ref_raw(m)); }
+
+// max(a, b, c) in one instruction.  fmaxf would first quiet every input
+// (one more instruction each): the compiler cannot tell that floats made
+// from bf16 bits by shifts are not signalling NaNs.  NaN logits are outside
+// the contract; -inf is handled like any value.
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
 
@@ -88,15 +109,17 @@ __device__ __forceinline__ void merge_ms(float &m, float &s, float &t, float m2,
   const float M = fmaxf(m, m2);
   if (M == -INFINITY) return;     // both empty so far
   float a = 0.f, b = 0.f, ta = 0.f, tb = 0.f;
-  const float rM = ref_of(M);
+  // (the product by a positive constant keeps the order, so the larger of the
+  // two references is ref_of(M))
+  const float r = ref_raw(m), r2 = ref_raw(m2), rM = max3(r, r2, -FLT_MAX);
   if (m != -INFINITY) {
-    const float d = ref_of(m) - rM;
+    const float d = at_least_lowest(r) - rM;
     const float f = __builtin_amdgcn_exp2f(d);
     a = s * f;
     if (ENT) ta = f * __builtin_fmaf(d, s, t);
   }
   if (m2 != -INFINITY) {
-    const float d = ref_of(m2) - rM;
+    const float d = at_least_lowest(r2) - rM;
     const float f = __builtin_amdgcn_exp2f(d);
     b = s2 * f;
     if (ENT) tb = f * __builtin_fmaf(d, s2, t2);
@@ -119,16 +142,6 @@ __device__ __forceinline__ void merge(float &m, float &s, float &t, int32_t &i, 
 // H = -sum p ln p with p = 2^y / s, i.e. ln 2 (log2 s - t / s).
 __device__ __forceinline__ float entropy_nats(float s, float t) {
   return 0.69314718055994531f * (log2f(s) - t / s);
-}
-
-// max(a, b, c) in one instruction.  fmaxf would first quiet every input
-// (one more instruction each): the compiler cannot tell that floats made
-// from bf16 bits by shifts are not signalling NaNs.  NaN logits are outside
-// the contract; -inf is handled like any value.
-__device__ __forceinline__ float max3(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
 }
 
 // Maximum of the 8 kU logits of one iteration, three at a time (a tree of
@@ -314,7 +327,8 @@ __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
         it_max = mark;
       }
       if (x != -INFINITY) {
-        const float y = __builtin_fmaf(x, kLog2e, nref);
+        float y = __builtin_fmaf(x, kLog2e, nref);
+        if (ENT) y = fmaxf(y, kYMin);    // (the type's lowest value overflows here: 0 * -inf)
         const float e = __builtin_amdgcn_exp2f(y);
         s += e;
         if (ENT) t = __builtin_fmaf(e, y, t);
