@@ -272,21 +272,26 @@ __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
   float nref = 0.f;      // -ref_of(m), 0 while m is -inf
   int32_t it_max = -1;
   int32_t it = 0;
+  // A new maximum, found at `mark`: the sums so far relative to it.
+  auto raise = [&](float top, int32_t mark) {
+    const float ref = ref_of(top);
+    if (m != -INFINITY) {
+      const float d = -nref - ref;
+      const float f = __builtin_amdgcn_exp2f(d);
+      if (ENT) t = f * __builtin_fmaf(d, s, t);
+      s *= f;
+    } else {         // only -inf so far (whose terms may have made t NaN: 0 * -inf)
+      s = 0.f;
+      t = 0.f;
+    }
+    m = top;
+    nref = -ref;
+    it_max = mark;
+  };
   // One iteration's 16 logits of this thread into the running (m, s, t).
   auto accumulate = [&](const float (&x)[kU][8], auto clamp) {
     const float cm = max_iter(x);
-    if (cm > m) {
-      const float ref = ref_of(cm);
-      if (m != -INFINITY) {     // (while m is -inf, s = t = 0)
-        const float d = -nref - ref;
-        const float f = __builtin_amdgcn_exp2f(d);
-        if (ENT) t = f * __builtin_fmaf(d, s, t);
-        s *= f;
-      }
-      m = cm;
-      nref = -ref;
-      it_max = it;
-    }
+    if (cm > m) raise(cm, it);
     float acc = 0.f, acct = 0.f;
 #pragma unroll
     for (int j = 0; j < kU; ++j)
@@ -314,18 +319,10 @@ __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
     // a thread's one logit of the head (visited first: the row's lowest
     // indices) or of the tail (visited last)
     auto single = [&](float x, int32_t mark) {
-      if (x > m) {
-        const float ref = ref_of(x);
-        if (m != -INFINITY) {
-          const float d = -nref - ref;
-          const float f = __builtin_amdgcn_exp2f(d);
-          if (ENT) t = f * __builtin_fmaf(d, s, t);
-          s *= f;
-        }
-        m = x;
-        nref = -ref;
-        it_max = mark;
-      }
+      // (a NaN counts as a maximum below every logit, so that a thread that
+      // holds nothing else does not lose it in the merge)
+      const float top = x == x ? x : -FLT_MAX;
+      if (top > m) raise(top, mark);
       if (x != -INFINITY) {
         float y = __builtin_fmaf(x, kLog2e, nref);
         if (ENT) y = fmaxf(y, kYMin);    // (the type's lowest value overflows here: 0 * -inf)
@@ -359,8 +356,9 @@ __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
             }
           }
         }
-        // clamped: the missing units' -inf must not reach the entropy sum
-        if constexpr (decltype(partial)::value) accumulate(x, std::true_type{});
+        // clamped with entropy only: the missing units' -inf must not reach its
+        // sum.  Without, a clamp would turn a NaN logit into probability 0.
+        if constexpr (ENT && decltype(partial)::value) accumulate(x, std::true_type{});
         else accumulate(x, clamp);
         ++it;
       };

@@ -120,3 +120,25 @@ def test_masked_logits(gpu, vocab, mask):
         for got in (c, u["conf"]):
             assert np.max(np.abs(got.cpu().numpy() - ref_c) / ref_c) <= 1e-6, off
         assert np.max(np.abs(u["entropy"].cpu().numpy() - ref_h)) <= 1e-5, off
+
+
+@pytest.mark.parametrize("vocab", [2, 9, 17, 1000, 4103, 5000, 9001, 50001])
+def test_a_nan_logit_keeps_the_token(gpu, vocab):
+    """One NaN in a row of finite logits, at either end or anywhere: without
+    entropies its confidence is NaN, which clears no threshold, whichever thread
+    and iteration meets it."""
+    rng = np.random.default_rng(vocab)
+    rows, stride = 32, vocab + 1 + vocab % 2
+    x = rng.normal(0.0, 3.0, size=(rows, vocab)).astype(np.float32)
+    ends = [c % vocab for e in range(9) for c in (e, vocab - 1 - e)]
+    for r in range(rows):
+        x[r, ends[r] if r < len(ends) else rng.integers(0, vocab)] = np.nan
+    x = torch.from_numpy(x).to(torch.bfloat16)
+    cur = torch.full((rows,), vocab, dtype=torch.int32, device=DEV)      # differs from every prediction
+    for off in range(8):
+        d = torch.zeros(8 + rows * stride + 8, dtype=torch.bfloat16)
+        d[off:off + rows * stride].view(rows, stride)[:, :vocab] = x
+        d = d.to(DEV)[off:off + rows * stride].view(rows, stride)
+        n, c, ch = gpu.edit_select(d, cur, 0.0, vocab=vocab)
+        torch.cuda.synchronize()
+        assert bool(torch.isnan(c).all()) and bool((n == cur).all()) and not bool(ch.any()), off
