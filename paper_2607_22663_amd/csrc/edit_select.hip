@@ -28,9 +28,10 @@
 // What bounds it: HBM, with the VALU close behind (64 logits cost about 32
 // cycles of a SIMD, half of them the exponential, 36 with the entropy; at
 // 6.8 TB/s a SIMD has 40).  So the loop keeps no per-iteration copies (two
-// register sets in turn) and forms the reference only when the maximum moves:
-// 2048 x 131072 with entropy 99.6 -> 95.5 us for the whole update, 512 x
-// 131072 without 27.0 -> 25.5 us, 8192 x 131072 313.9 -> 312.5 us (6.87 TB/s).
+// register sets in turn; one where that is better, see the launch) and forms
+// the reference only when the maximum moves: 2048 x 131072 with entropy 91.5 ->
+// 86.3 us for the whole update, 512 x 131072 without 25.3 -> 22.8 us, 8192 x
+// 131072 312.9 -> 311.0 us (6.90 TB/s).
 // Every row takes 16-byte loads wherever it starts (its up to 7 logits before
 // and after the 16-byte grid are read one per thread): 992 rows of 100003
 // packed behind each other, with entropy, 276.7 -> 48.4 us; and an iteration
@@ -112,14 +113,16 @@ __device__ __forceinline__ void merge_ms(float &m, float &s, float &t, float m2,
   // (the product by a positive constant keeps the order, so the larger of the
   // two references is ref_of(M))
   const float r = ref_raw(m), r2 = ref_raw(m2), rM = max3(r, r2, -FLT_MAX);
+  // (without the entropy sum an overflowed reference, of a sum that is 0, may
+  // stay: d = -inf, f = 0)
   if (m != -INFINITY) {
-    const float d = at_least_lowest(r) - rM;
+    const float d = (ENT ? at_least_lowest(r) : r) - rM;
     const float f = __builtin_amdgcn_exp2f(d);
     a = s * f;
     if (ENT) ta = f * __builtin_fmaf(d, s, t);
   }
   if (m2 != -INFINITY) {
-    const float d = at_least_lowest(r2) - rM;
+    const float d = (ENT ? at_least_lowest(r2) : r2) - rM;
     const float f = __builtin_amdgcn_exp2f(d);
     b = s2 * f;
     if (ENT) tb = f * __builtin_fmaf(d, s2, t2);
@@ -226,7 +229,9 @@ __device__ __forceinline__ void decide(const EsParams &p, int64_t row, float m, 
   p.changed[row] = change ? 1 : 0;
 }
 
-template <bool VEC, bool ENT, int kT>
+// DEEP: the next iteration is requested before the current one is unpacked (two
+// register sets in turn, two iterations in flight), otherwise after it.
+template <bool VEC, bool ENT, int kT, bool DEEP>
 __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
   __shared__ float sh_m[kT / 64];
   __shared__ float sh_s[kT / 64];
@@ -258,14 +263,15 @@ __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
   const int64_t u1 = last ? (VEC ? g_end / 8 : (g_end + 7) / 8) : (chunk + 1) * chunk_units;
   const int64_t c1 = min(g_end, u1 * 8);              // end of the units' logits on the grid
 
-  // This thread's logit of the head and of the tail, if it has one: requested
-  // before the first vectors by every workgroup (a branch around the loads
-  // would wait for them in it) and used after them.  Relaxed atomic loads
-  // stay where they are written; every address lies in the row.
+  // This thread's logit of the head and of the tail, if it has one (otherwise
+  // the row's first, whose page is read anyway): requested before the first
+  // vectors by every workgroup (a branch around the loads would wait for them
+  // in it) and used after them.  Relaxed atomic loads stay where they are
+  // written; every address lies in the row.
   uint32_t raw_h = 0, raw_t = 0;
   if constexpr (VEC) {
-    raw_h = load16b(rowp + min(static_cast<int64_t>(tid), p.vocab - 1));
-    raw_t = load16b(rowp + min(tail0 + tid, p.vocab - 1));
+    raw_h = load16b(rowp + (tid < head ? tid : 0));
+    raw_t = load16b(rowp + (tid < tail ? tail0 + tid : 0));
   }
 
   float m = -INFINITY, s = 0.f, t = 0.f;
@@ -280,7 +286,7 @@ __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
       const float f = __builtin_amdgcn_exp2f(d);
       if (ENT) t = f * __builtin_fmaf(d, s, t);
       s *= f;
-    } else {         // only -inf so far (whose terms may have made t NaN: 0 * -inf)
+    } else if (ENT) {     // only -inf so far, whose terms made t NaN (0 * -inf)
       s = 0.f;
       t = 0.f;
     }
@@ -307,7 +313,7 @@ __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
     if (ENT) t += acct;
   };
   // The whole chunk, the next iteration's loads issued before the current
-  // one is reduced.
+  // one is summed.
   auto pass = [&](auto clamp) {
     m = -INFINITY;
     s = 0.f;
@@ -335,14 +341,19 @@ __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
       // Iterations 0 .. n - 1 of per_iter units, the last perhaps of fewer.  A
       // request past the last unit reads the last one again, so that
       // every request is unconditional (the compiler would otherwise wait for
-      // all loads in flight where a skipped request and a made one meet).  Two
-      // register sets in turn, so that no vector is copied.
+      // all loads in flight where a skipped request and a made one meet).
       const int32_t units = static_cast<int32_t>(max(u1 - u0, static_cast<int64_t>(0)));
       const int32_t n_full = units / per_iter, n = (units + per_iter - 1) / per_iter;
       u32x4 wa[kU], wb[kU];
+      // 32-bit byte offsets from the chunk's start (a row is below 4 GB): 87
+      // instructions an iteration instead of 93 with 64-bit unit indices.
+      const __attribute__((address_space(1))) char *base = (const __attribute__((address_space(1))) char *)(grid + u0 * 8);
+      const uint32_t last_off = static_cast<uint32_t>(units - 1) * 16u;
       auto request = [&](u32x4 (&w)[kU], int32_t i) {
+        const uint32_t at = (static_cast<uint32_t>(i) * per_iter + tid) * 16u;
 #pragma unroll
-        for (int j = 0; j < kU; ++j) w[j] = load16(grid, u0 + min(i * per_iter + j * kT + tid, units - 1));
+        for (int j = 0; j < kU; ++j)
+          w[j] = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4 *)(base + min(at + j * kT * 16u, last_off)));
       };
       auto reduce_iter = [&](const u32x4 (&w)[kU], auto partial) {
         float x[kU][8];
@@ -364,17 +375,29 @@ __global__ __launch_bounds__(kT) void edit_select_kernel(EsParams p) {
       };
       if (n > 0) request(wa, 0);
       if (tid < head) single(bf16_lo(raw_h), kHeadIter);
-      while (it + 2 <= n_full) {
-        request(wb, it + 1);
-        reduce_iter(wa, std::false_type{});
-        request(wa, it + 1);
-        reduce_iter(wb, std::false_type{});
-      }
-      while (it < n) {        // at most one whole iteration and one partial one, in one body
-        request(wb, it + 1);
-        reduce_iter(wa, std::true_type{});
+      if constexpr (DEEP) {
+        while (it + 2 <= n_full) {       // the register sets in turn, so that no vector is copied
+          request(wb, it + 1);
+          reduce_iter(wa, std::false_type{});
+          request(wa, it + 1);
+          reduce_iter(wb, std::false_type{});
+        }
+        while (it < n) {      // at most one whole iteration and one partial one, in one body
+          request(wb, it + 1);
+          reduce_iter(wa, std::true_type{});
 #pragma unroll
-        for (int j = 0; j < kU; ++j) wa[j] = wb[j];
+          for (int j = 0; j < kU; ++j) wa[j] = wb[j];
+        }
+      } else {
+        while (it < n_full) {
+          float x[kU][8];
+#pragma unroll
+          for (int j = 0; j < kU; ++j) unpack8(wa[j], x[j]);
+          request(wa, it + 1);
+          accumulate(x, clamp);
+          ++it;
+        }
+        if (it < n) reduce_iter(wa, std::true_type{});
       }
       if (tid < tail) single(bf16_lo(raw_t), kTailIter);
     } else {
@@ -629,21 +652,35 @@ __global__ __launch_bounds__(256) void threshold_block_wave_kernel(EsParams p) {
 
 template <bool ENT>
 hipError_t launch_rows(const EsParams &p, bool vector_loads, hipStream_t stream) {
-  const dim3 grid(static_cast<unsigned>(p.rows * p.chunks));
+  const int64_t wgs = p.rows * p.chunks;
+  const dim3 grid(static_cast<unsigned>(wgs));
   // Few rows, each by one workgroup: twice the threads, since a workgroup then
   // has its CU to itself or nearly (256 x 131072: 16.5 us for the call, 18.7
   // with four times the threads or with four loads per thread; from 512 rows
   // on the smaller workgroups are better, 24.8 against 28.0 us).
   if (p.chunks == 1 && p.rows < kEsTargetWgs) {
     if (vector_loads)
-      hipLaunchKernelGGL((edit_select_kernel<true, ENT, 2 * kEsThreads>), grid, dim3(2 * kEsThreads), 0, stream, p);
+      hipLaunchKernelGGL((edit_select_kernel<true, ENT, 2 * kEsThreads, true>), grid, dim3(2 * kEsThreads), 0, stream, p);
     else
-      hipLaunchKernelGGL((edit_select_kernel<false, ENT, 2 * kEsThreads>), grid, dim3(2 * kEsThreads), 0, stream, p);
-  } else if (vector_loads) {
-    hipLaunchKernelGGL((edit_select_kernel<true, ENT, kEsThreads>), grid, dim3(kEsThreads), 0, stream, p);
-  } else {
-    hipLaunchKernelGGL((edit_select_kernel<false, ENT, kEsThreads>), grid, dim3(kEsThreads), 0, stream, p);
+      hipLaunchKernelGGL((edit_select_kernel<false, ENT, 2 * kEsThreads, true>), grid, dim3(2 * kEsThreads), 0, stream, p);
+    return hipGetLastError();
   }
+  // Between two and five workgroups per CU, one iteration in flight per wave
+  // and not two: with two, the CUs that hold one workgroup more than the others
+  // get no more of the memory rate than those and finish late (all of it goes
+  // round-robin by CU), with one every workgroup runs at its own pace.  Measured,
+  // two in flight / one, us, without entropy: 528 x 65536 14.8 / 15.6, 640 x
+  // 131072 28.4 / 28.1, 784 x 131072 37.9 / 34.5, 832 x 151936 45.3 / 41.6, 1152 x
+  // 131072 50.9 / 48.6, 1408 x 131072 58.9 / 58.7, 1536 x 131072 61.7 / 62.7, 512 x
+  // 131072 22.8 / 25.6; with it: 528 x 131072 30.7 / 29.7, 784 x 131072 43.1 / 38.6.
+  // A row of one iteration has no next one: 8192 x 4096 without 23.7 / 23.6.
+  const bool deep = p.chunk_len > kEsThreads * kU * 8 && (wgs < (ENT ? kEsTargetWgs + 1 : 640) || wgs >= 1408);
+  if (!vector_loads)
+    hipLaunchKernelGGL((edit_select_kernel<false, ENT, kEsThreads, true>), grid, dim3(kEsThreads), 0, stream, p);
+  else if (deep)
+    hipLaunchKernelGGL((edit_select_kernel<true, ENT, kEsThreads, true>), grid, dim3(kEsThreads), 0, stream, p);
+  else
+    hipLaunchKernelGGL((edit_select_kernel<true, ENT, kEsThreads, false>), grid, dim3(kEsThreads), 0, stream, p);
   return hipGetLastError();
 }
 

@@ -70,3 +70,25 @@ def test_update_merges_chunks(gpu, rows, vocab, block, entropy):
     assert np.max(np.abs(out["conf"].cpu().numpy() - ref["conf"]) / ref["conf"]) <= 1e-6
     if entropy:
         assert np.max(np.abs(out["entropy"].cpu().numpy() - ref["entropy"])) <= 1e-5
+
+
+@pytest.mark.parametrize("vocab", [1, 9, 4095, 4096, 4097, 8192, 12300, 40961])
+@pytest.mark.parametrize("rows", [512, 528, 640, 1408])
+def test_one_or_two_iterations_in_flight(gpu, rows, vocab):
+    """Both forms of the row loop, on either side of the rows where one takes
+    over from the other (513 with entropies, 640 without, 1408): no whole
+    iteration (4096 logits a workgroup), whole ones only, and a remainder, with
+    rows on and off the 16-byte grid."""
+    for stride in ((vocab + 7) // 8 * 8, vocab + 1 + vocab % 2):
+        x = torch.full((rows, stride), float("inf"), dtype=torch.bfloat16, device=DEV)
+        x[:, :vocab], cur = _logits(rows, vocab, rows + vocab)
+        n, c, ch = gpu.edit_select(x, cur, 0.5, vocab=vocab)
+        u = gpu.threshold_update(x, cur, vocab, 16, 0.5, 0.0, vocab=vocab, with_entropy=True)
+        torch.cuda.synchronize()
+        pick = np.unique(np.linspace(0, rows - 1, 24).astype(int))
+        xp = x[pick, :vocab].cpu()
+        rn, rc, rch = oracle.edit_select(xp, cur[pick].cpu(), 0.5)
+        assert np.array_equal(n[pick].cpu().numpy(), rn) and np.array_equal(ch[pick].cpu().numpy(), rch)
+        for got in (c, u["conf"]):
+            assert np.max(np.abs(got[pick].cpu().numpy() - rc) / rc) <= 1e-6
+        assert np.max(np.abs(u["entropy"][pick].cpu().numpy() - oracle.entropy.row_entropy(xp))) <= 1e-5
