@@ -597,13 +597,27 @@ void row_plan(int64_t rows, int64_t vocab, int32_t *chunks, int64_t *chunk_len) 
 
 void edit_select_plan(int64_t rows, int64_t vocab, int32_t *chunks, int64_t *chunk_len) {
   row_plan(rows, vocab, chunks, chunk_len);
+  const int64_t c = *chunks;
+  if (c <= 1) return;
   // One workgroup per row where cutting rows saves less than its merge launch
-  // costs (4 us): a workgroup alone on its CU reduces about 31 KB/us (its
-  // CU's VALU), all of them together at most 5.5 MB/us, so while
-  //   2 vocab / 31e3 <= 4 + rows * 2 vocab / 5.5e6   (us).
-  // Measured, cut + merge against whole rows: 256 x 131072 20.6 / 16.5 us, 128
-  // x 131072 15.9 / 14.1, 64 x 131072 12.3 / 12.8, 64 x 32000 10.4 / 8.4.
-  if (*chunks > 1 && vocab * (177 - rows) <= 177 * 62000) {
+  // costs.  Two launches take 10 us whatever they do, a workgroup alone on its
+  // CU reduces 80000 logits in that time.  For longer rows what counts is the
+  // part of a row that the fullest CU is spared, of ceil(rows / 256) whole rows
+  // against ceil(rows c / 256) chunks (1 - 2 / c for up to 64 rows, 3/8 to 5/8 up
+  // to 128, 1/4 up to 170, 1/2 from 257 to 384, otherwise none): it pays from 50000
+  // logits on.  Measured, us, cut + merge / whole rows:
+  //   rows      80000         100000        131072        262144
+  //     1   10.2 /  8.1   10.1 /  8.9   10.1 / 10.0   10.1 / 15.7
+  //    64   10.4 / 10.0   10.1 / 11.0    9.8 / 12.5   12.0 / 19.2
+  //   128   10.3 / 10.1   11.5 / 11.4   12.0 / 13.0   16.5 / 19.9
+  //   160   11.8 / 10.3   12.8 / 11.6   13.7 / 13.3   19.7 / 20.7
+  //   256   13.5 / 11.0   14.9 / 12.6   16.7 / 15.3   26.2 / 24.7
+  //   288   14.9 / 14.4   16.9 / 17.4   18.9 / 20.6   31.1 / 35.8
+  //   384   16.0 / 15.4   18.6 / 18.4   21.5 / 22.2   35.9 / 37.5
+  //   416   17.1 / 15.7   20.5 / 19.0   23.5 / 22.9   40.0 / 40.7
+  const int64_t spared = (rows + 255) / 256 * c - (rows * c + 255) / 256;   // in chunks
+  const bool whole = vocab <= 80000 || vocab * spared <= 50000 * c;
+  if (whole) {
     *chunks = 1;
     *chunk_len = (vocab + 7) / 8 * 8;
   }

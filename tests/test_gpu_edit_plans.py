@@ -26,10 +26,16 @@ def _logits(rows, vocab, seed):
     return x, cur
 
 
-# (rows, vocab): 62350 / 97125 / 224025 are where the rule turns at 1, 64 and 128 rows
-@pytest.mark.parametrize("rows,vocab", [(1, 62352), (1, 62353), (1, 4096), (1, 4097), (64, 97119), (64, 97123), (128, 131072),
-                                        (176, 131072), (177, 131073), (511, 20000), (512, 20000), (513, 8191), (3, 200003)])
-def test_edit_select_plans(gpu, rows, vocab):
+# (rows, vocab, whether its rows are cut): both sides of the turns of the rule,
+# at 80000 logits for the fewest rows, 100000 at 128 and 288, 200000 at 160
+@pytest.mark.parametrize("rows,vocab,cut", [
+    (1, 80000, False), (1, 80001, True), (1, 4096, False), (1, 4097, False), (3, 200003, True),
+    (64, 80000, False), (64, 80001, True), (128, 100000, False), (128, 100001, True), (160, 200000, False),
+    (160, 200001, True), (176, 131072, False), (256, 131073, False), (257, 80000, False), (288, 100000, False),
+    (288, 100001, True), (384, 131072, True), (385, 131072, False), (511, 20000, False), (512, 20000, False),
+    (513, 8191, False)])
+def test_edit_select_plans(gpu, rows, vocab, cut):
+    assert (gpu.load().mbe_edit_select_workspace_size(rows, vocab) > 0) == cut
     x, cur = _logits(rows, vocab, rows + vocab)
     n, c, ch = gpu.edit_select(x, cur, 0.5)
     torch.cuda.synchronize()
