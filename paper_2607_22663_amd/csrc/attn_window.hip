@@ -463,10 +463,14 @@ __global__ __launch_bounds__(kT, 1) void window_attention_kernel(AttnParams p) {
   // has the matrix cores to itself.  Its path is apart from the others' and
   // ends here: joined again it would cost them registers (190-300 bytes of
   // scratch), as it does in the pipelined kernels, which compute their padding.
+  // It adds 2-4 KB of code (one copy of its pass, in a loop).  Padded tiles gain:
   // 8 x 4096 keys, 3 blocks of 32 with 4 query heads per KV head (384 rows in
-  // two tiles of 256): 53.7 -> 51.8 us; 16 x 4000, 2 blocks, 1 query head per
-  // KV head (64 rows of 128): 56.1 -> 54.5 us; full tiles unchanged.
-  if (!PIPE && __builtin_amdgcn_ballot_w64(any_valid) == 0) {
+  // two tiles of 256) 51.7 -> 50.1 us; 16 x 4000, 2 blocks, 1 query head per KV
+  // head (64 rows of 128) 36.2 -> 34.4; full tiles are unchanged, but for one
+  // kernel, which the other waves' registers come out worse in (28 x 20089 keys,
+  // 128 rows, D = 64: 107 -> 130 us), and which goes without.
+  constexpr bool kIdleWaves = !PIPE && !(D == 64 && MODE == 0 && KS == 2 && !VT);
+  if (kIdleWaves && __builtin_amdgcn_ballot_w64(any_valid) == 0) {
     const int ntiles = tiles_to(min(n_all, kb + p.kv_chunk));
     uint32_t koff[Tile<D>::kWaveLoads], voff;
     k_load_offsets<D>(koff, wpart);
@@ -503,10 +507,10 @@ __global__ __launch_bounds__(kT, 1) void window_attention_kernel(AttnParams p) {
       }
       lds_barrier();
     };
-    if (ntiles > 0) pass();
-    if (wg_any(false)) {      // the rerun: the row maxima, then everything again
-      pass();
-      pass();
+    // once; when the others rerun, for their row maxima and for everything again
+    for (int n = 0; n < 3; ++n) {
+      if (ntiles > 0) pass();
+      if (n == 0 && !wg_any(false)) break;
     }
     if constexpr (KS == 2) lds_barrier();   // the hand-over of the second key blocks
     return;
