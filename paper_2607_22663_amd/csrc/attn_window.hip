@@ -1405,15 +1405,16 @@ __global__ __launch_bounds__(kT, 1) void window_attention_short_kernel(AttnParam
 
 // Split-KV merge, run after the main kernel when some sequence was split (the
 // kernel boundary makes every partial result visible; no cross-workgroup
-// fences inside the main kernel).  Block (x, b) merges items x*256 .. of
-// sequence b, an item being kMergeDims dims of one (window row, query head):
+// fences inside the main kernel).  Block (x, b) merges the 256 / L items from
+// x * 256 / L on of sequence b, an item being kMergeDims dims of one (window row,
+// query head):
 //   M = max m_s,  O = sum 2^(m_s-M) O_s / sum 2^(m_s-M) l_s   (split order).
 //
-// The splits of an item are shared by L lanes (1, 2, 4 or 8: the fewest with
-// at most 8 splits each), so that one round of loads holds them all; the lanes'
-// sums are then combined in a fixed order.  A short call is launch and round
-// trips only, and 17 splits by one lane were three rounds: 1 x
-// 2048 keys 18.8 -> 16.9 us a call; up to 8 splits are as they were.
+// The splits of an item are shared by L lanes (1, 2, 4 or 8, see the launch); the
+// lanes' sums are then combined in a fixed order.  A lane reads 8 splits in one
+// round of loads.  A short call is launch and round trips only, and 17 splits
+// by one lane were three rounds: 1 x 2048 keys 18.3 -> 16.0 us a call, 1 x 8192
+// 33.1 -> 27.2; up to 8 splits are as they were.
 constexpr int kMergeDims = 8;   // dims per merge thread: two 16-byte loads per split, one 16-byte store
 template <int D, int L>
 __global__ __launch_bounds__(256) void window_attention_merge_kernel(AttnParams p) {
@@ -1571,10 +1572,17 @@ hipError_t launch_t(const AttnParams &p, hipStream_t stream) {
     const dim3 mgrid(static_cast<unsigned>((items * L + 255) / 256), static_cast<unsigned>(p.batch));
     hipLaunchKernelGGL((window_attention_merge_kernel<D, L>), mgrid, dim3(256), 0, stream, p);
   };
-  // (with more than 2^18 items the CUs are full: nothing to gain)
-  if (p.splits <= 8 || items * p.batch > (1 << 18)) merge(std::integral_constant<int, 1>{});
-  else if (p.splits <= 16) merge(std::integral_constant<int, 2>{});
-  else if (p.splits <= 32) merge(std::integral_constant<int, 4>{});
+  // Lanes per item: the fewest that hold the plan's splits in one round of loads
+  // each, but no more workgroups for it than CUs (2^16 lanes): with more, the
+  // empty ones of a plan whose bounds are wide, and the loads of a full one, cost
+  // more than the rounds.  1 lane / as many as hold the splits / this rule, us:
+  // 1 x 6000 keys, 8 blocks of 16, 32 splits 32.5 / 35.6 / 30.3; 3 x 3200, 17
+  // splits, 98304 items 31.5 / 34.2 / 31.5; 4 x 18464, 33 splits 30.4 / 28.9 / 28.9.
+  int lanes = 1;
+  while (lanes < 8 && 8 * lanes < p.splits && items * p.batch * 2 * lanes <= (1 << 16)) lanes *= 2;
+  if (lanes == 1) merge(std::integral_constant<int, 1>{});
+  else if (lanes == 2) merge(std::integral_constant<int, 2>{});
+  else if (lanes == 4) merge(std::integral_constant<int, 4>{});
   else merge(std::integral_constant<int, 8>{});
   return hipGetLastError();
 }

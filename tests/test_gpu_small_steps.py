@@ -25,6 +25,18 @@ def test_merge_lanes(gpu, nsplit, D):
         assert_attn_close(out, A.oracle_case(case, mode), f"{nsplit} splits D {D} {mode}")
 
 
+@pytest.mark.parametrize("W,hq,nsplit", [(128, 32, 17), (32, 16, 33), (32, 16, 70), (32, 8, 70)])
+def test_merge_lanes_of_many_splits(gpu, W, hq, nsplit):
+    """More items than the lanes of one workgroup per CU leave room for: one, two
+    (33 and 70 splits) and four lanes with more than 8 splits each."""
+    n = nsplit * 64
+    spec = synth.AttnSpec(3, 16, W // 16, ("fixed", 0), hq, 4, 128)
+    case = synth.make_attention_case(spec, nsplit, prefix_lens=[n - W, n // 2, 1], window_lens=[W, 16, W],
+                                     tail_fill=float("nan"))
+    out = A.run_case(gpu, case, "bidir", kv_split_tokens=64)
+    assert_attn_close(out, A.oracle_case(case, "bidir"), f"{nsplit} splits W {W} heads {hq}")
+
+
 @pytest.mark.parametrize("num_blocks", [1, 4, 63, 64, 65, 130])
 @pytest.mark.parametrize("mode", ["changed", "changed_and_later"])
 def test_refresh_flags(gpu, num_blocks, mode):
