@@ -268,6 +268,8 @@ mbe_status plan_attention(const mbe_paged_kv *kv, const mbe_attn_opts *o, int32_
       n_seq[b] = W > 0 ? P + W : 0;
     }
   }
+  bool ragged = false;
+  for (size_t b = 1; b < n_seq.size(); ++b) ragged = ragged || n_seq[b] != n_seq[0];
 
   int64_t chunk = o->kv_split_tokens;
   bool rule_split = false;      // the default rule below cut the key ranges to fill the CUs
@@ -287,14 +289,26 @@ mbe_status plan_attention(const mbe_paged_kv *kv, const mbe_attn_opts *o, int32_
       }
       return u;
     };
+    // Workgroups of that plan: every split and query tile within the bounds,
+    // unless a dispatch table (ragged lengths, see below) names the units.
+    auto workgroups = [&](int64_t c) {
+      const int64_t all = static_cast<int64_t>(o->batch) * kv->num_kv_heads * std::max<int64_t>(1, tiles_of(rows)) *
+                          ((max_kv + c - 1) / c);
+      return ragged && all < mbe::kNoUnit ? units(c) : all;
+    };
     const int64_t c_max = std::max<int64_t>(kMinChunk, (max_kv + mbe::kKeyTile - 1) / mbe::kKeyTile * mbe::kKeyTile);
     // Little work: 128-row tiles in units of at most 4 key tiles that all run
-    // at once, on the kernel for such units; the shortest that fit.
+    // at once, on the kernel for such units; the shortest that fit.  Not where the
+    // bounds are so much wider than the lengths that smaller tiles only make
+    // more empty workgroups: 1 x 200 keys, 1 of 8 blocks, bounds of 32768 keys
+    // 22.3 us with 4128 workgroups, 32.6 with 8256; of 4096 keys 14.5 / 14.5 with
+    // 544 / 1088; 2 x 100, 2 of 8 blocks, 4096 keys 18.3 / 22.5 with 2176 / 4352.
     const int32_t wide_tile = pl->row_tile;
     if (pipeline_override() < 0) {
       pl->row_tile = mbe::kShortRows;
       for (int64_t c = kMinChunk; c <= mbe::kShortTiles * mbe::kKeyTile && chunk == 0; c += mbe::kKeyTile)
-        if (units(c) <= kConcurrentUnits) chunk = c;
+        if (units(c) <= kConcurrentUnits && (wide_tile == mbe::kShortRows || workgroups(c) <= 5 * kConcurrentUnits))
+          chunk = c;
     }
     if (chunk != 0) {
       rule_split = true;
@@ -328,26 +342,22 @@ mbe_status plan_attention(const mbe_paged_kv *kv, const mbe_attn_opts *o, int32_
   // Equal lengths are balanced by the formula already, and large batches
   // gained nothing from a table.
   UnitSchedule sched;
-  if (host && rule_split) {
-    bool ragged = false;
-    for (int b = 1; b < o->batch; ++b) ragged = ragged || n_seq[b] != n_seq[0];
-    if (ragged) {
-      std::vector<SeqWork> seqs(o->batch);
-      for (int b = 0; b < o->batch; ++b) {
-        const int64_t W = fixed_window >= 0 ? fixed_window : o->host_window_lens[b];
-        seqs[b] = {n_seq[b], W, static_cast<int32_t>(tiles_of(pl->group * W))};
-      }
-      schedule_units(seqs, kv->num_kv_heads, pl->qtiles, o->num_q_heads, kv->head_dim, max_kv, chunk, &sched);
-      UnitSchedule alt;
-      const int64_t d = chunk;
-      for (int64_t cand : {d * 7 / 8, d * 3 / 4}) {
-        const int64_t c = std::max<int64_t>(kMinChunk, (cand + mbe::kKeyTile - 1) / mbe::kKeyTile * mbe::kKeyTile);
-        if (c >= d || !alternates) continue;
-        schedule_units(seqs, kv->num_kv_heads, pl->qtiles, o->num_q_heads, kv->head_dim, max_kv, c, &alt);
-        if (alt.finish >= 0 && (sched.finish < 0 || alt.finish < sched.finish * (1.0 - kMinPlanGain))) {
-          chunk = c;
-          sched = alt;
-        }
+  if (ragged && rule_split) {
+    std::vector<SeqWork> seqs(o->batch);
+    for (int b = 0; b < o->batch; ++b) {
+      const int64_t W = fixed_window >= 0 ? fixed_window : o->host_window_lens[b];
+      seqs[b] = {n_seq[b], W, static_cast<int32_t>(tiles_of(pl->group * W))};
+    }
+    schedule_units(seqs, kv->num_kv_heads, pl->qtiles, o->num_q_heads, kv->head_dim, max_kv, chunk, &sched);
+    UnitSchedule alt;
+    const int64_t d = chunk;
+    for (int64_t cand : {d * 7 / 8, d * 3 / 4}) {
+      const int64_t c = std::max<int64_t>(kMinChunk, (cand + mbe::kKeyTile - 1) / mbe::kKeyTile * mbe::kKeyTile);
+      if (c >= d || !alternates) continue;
+      schedule_units(seqs, kv->num_kv_heads, pl->qtiles, o->num_q_heads, kv->head_dim, max_kv, c, &alt);
+      if (alt.finish >= 0 && (sched.finish < 0 || alt.finish < sched.finish * (1.0 - kMinPlanGain))) {
+        chunk = c;
+        sched = alt;
       }
     }
   }

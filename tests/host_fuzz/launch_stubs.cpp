@@ -41,6 +41,13 @@ hipError_t launch_window_attention(const AttnParams &p, int head_dim, int mask_m
   REQUIRE(static_cast<int64_t>(p.splits) * p.kv_chunk >= static_cast<int64_t>(p.max_prefix) + p.max_window);
   REQUIRE(p.groups == static_cast<int64_t>(p.batch) * p.num_kv_heads * p.splits);
   REQUIRE(p.key_split == 1 || p.key_split == 2);
+  // tiles of 128 rows with two waves per 32 rows, or of 256.  The general kernel
+  // takes one query tile of 128 rows at most; the short one holds its units whole.
+  const int row_tile = p.key_split == 2 ? kShortRows : kRowsPerTile;
+  REQUIRE(static_cast<int64_t>(p.qtiles) * row_tile >= static_cast<int64_t>(p.group) * p.max_window);
+  REQUIRE(p.short_tiles == 0 || (p.key_split == 2 && p.kv_chunk <= p.short_tiles * kKeyTile));
+  REQUIRE(p.short_tiles != 0 || p.key_split == 1 || p.qtiles == 1);
+  REQUIRE(p.short_tiles <= kShortTiles);
   // split-KV partials: [splits][total_q][Hq][D] fp32, then [splits][total_q][Hq][2]
   if (p.splits > 1) {
     const char *base = reinterpret_cast<const char *>(p.part_o);
@@ -92,7 +99,7 @@ hipError_t launch_window_attention(const AttnParams &p, int head_dim, int mask_m
       const int W = p.fixed_window >= 0 ? p.fixed_window : fuzz::host_W[b];
       const int64_t n_all = static_cast<int64_t>(fuzz::host_P[b]) + W;
       const int64_t nsplit = std::min<int64_t>(p.splits, std::max<int64_t>(1, (n_all + p.kv_chunk - 1) / p.kv_chunk));
-      const bool work = W > 0 && static_cast<int64_t>(qtile) * kRowsPerTile < static_cast<int64_t>(p.group) * W &&
+      const bool work = W > 0 && static_cast<int64_t>(qtile) * row_tile < static_cast<int64_t>(p.group) * W &&
                         split < nsplit;
       if (work) REQUIRE(seen[u] == 1);
     }

@@ -435,3 +435,26 @@ def test_attention_plan_picks_the_kernel_variant(lib, monkeypatch):
     kv, opts, bad_opts, out = _kv(), _opts(), _opts(num_q_heads=5), ctypes.create_string_buffer(64)
     assert raw.mbe_window_attention_plan(ctypes.addressof(kv), ctypes.addressof(opts), None) == 1
     assert raw.mbe_window_attention_plan(ctypes.addressof(kv), ctypes.addressof(bad_opts), ctypes.addressof(out)) == 2
+
+
+def test_wide_bounds_do_not_halve_the_tiles(lib, monkeypatch):
+    """Lengths far below the bounds: the 128-row tiles of little work are taken
+    while their workgroups (every split and tile within the bounds) stay few, or a
+    dispatch table of ragged lengths names the units alone."""
+    monkeypatch.delenv("MBE_ATTN_PIPELINE", raising=False)
+
+    def plan(P, W, bound_p, bound_w, hkv=4, group=4):
+        kp = torch.empty((8, hkv, 16, 128), dtype=torch.bfloat16, device="meta")
+        vp = torch.empty((8, hkv, 128, 16), dtype=torch.bfloat16, device="meta")
+        pt = torch.empty((len(P), (bound_p + bound_w) // 16), dtype=torch.int32, device="meta")
+        p = mbe.window_attention_plan(group * hkv, kp, vp, pt, len(P), sum(W), max_prefix_len=bound_p,
+                                      max_window_len=bound_w, host_prefix_lens=P, host_window_lens=W)
+        return p["key_split"], p["workgroups"]
+
+    assert plan([200], [32], 256, 256) == (2, 128)
+    assert plan([200], [32], 4096, 256) == (2, 1088)
+    assert plan([200], [32], 32768, 256) == (1, 4128)
+    assert plan([200], [32], 32768, 32) == (2, 1032)               # 128 rows at most: the same tiles either way
+    assert plan([100, 100], [64, 64], 4096, 256, group=8) == (1, 2176)
+    assert plan([100, 150], [64, 64], 4096, 256, group=8) == (2, 64)
+    assert plan([100, 150], [64, 64], 131072, 256, group=8) == (1, 65664)     # unit indices beyond the table's 16 bits
