@@ -298,7 +298,7 @@ def window_attention_plan(num_q_heads, k_pages, v_pages, page_table, batch, tota
     d = {f: getattr(plan, f) for f, _ in AttnPlan._fields_}
     if plan.key_split == 2 and plan.kv_chunk <= 256 and os.environ.get("MBE_ATTN_PIPELINE", "")[:1] not in ("0", "1"):
         d["kernel"] = (f"window_attention_short_kernel<{k_pages.shape[3]},{mode},{int(layout == V_TOKEN_MAJOR)},"
-                       f"{2 if plan.kv_chunk <= 128 else 4}>")
+                       f"{plan.kv_chunk // 64}>")
         return d
     d["kernel"] = (f"window_attention_kernel<{k_pages.shape[3]},{mode},{plan.key_split},"
                    f"{int(layout == V_TOKEN_MAJOR)},{plan.pipelined}>")

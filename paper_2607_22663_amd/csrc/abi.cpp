@@ -489,12 +489,13 @@ int32_t key_split_of(const AttnPlan &pl) { return pl.row_tile == mbe::kShortRows
 
 // The kernel for units of a few key tiles takes every plan with 128-row tiles
 // and units of at most 4 tiles (the smallest calls, and short splits that a
-// caller forces).  Measured against the general kernel: 1 x 2048 keys with 2
-// blocks (136 units of 128 rows against 68 of 256) 22.3 -> 18.8 us a call.
+// caller forces).  Measured, us, the general kernel / this one: 1 x 2048 keys with
+// 2 blocks (68 units of 256 rows / 136 of 128) 22.3 / 18.8, 2 x 3000 30.0 / 24.0,
+// 16 x 400 30.8 / 25.1; forced splits of 64 keys, 1 x 4096 30.8 / 21.5.
 int32_t short_tiles_of(const AttnPlan &pl) {
   if (pl.row_tile != mbe::kShortRows || pl.kv_chunk > mbe::kShortTiles * mbe::kKeyTile || pipeline_override() >= 0)
     return 0;
-  return pl.kv_chunk <= 2 * mbe::kKeyTile ? 2 : 4;
+  return pl.kv_chunk / mbe::kKeyTile;
 }
 
 bool use_pipelined(const mbe_paged_kv *kv, const mbe_attn_opts *o, const AttnPlan &pl, int32_t window_bound,

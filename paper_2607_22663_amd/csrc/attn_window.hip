@@ -1157,7 +1157,7 @@ __device__ __forceinline__ void read_fields(const AttnParams &p) {
                "s"(p.splits), "s"(p.total_q), "s"(p.num_q_heads), "s"(p.num_pages), "s"(p.groups));
 }
 
-// The same attention for units of at most NT key tiles (2 or 4) and 128 rows:
+// The same attention for units of at most NT key tiles (1 to 4) and 128 rows:
 // the smallest calls, whose time is latency, not throughput.  Waves w and
 // w + 4 own the same 32 rows and take the first and the second 32-key block of
 // every tile (as with KS = 2 above).  Differences that the short length allows:
@@ -1165,9 +1165,12 @@ __device__ __forceinline__ void read_fields(const AttnParams &p) {
 // requested at once, right behind the lengths, and waited for twice (K and Q,
 // then V); all scores of a wave are held in registers, so the reference is
 // their true maximum and no sum can overflow (no rerun); and the code is short
-// and straight (10 KB against 36), as each launch fetches it anew.  What bounds
-// it: one round trip for the lengths, one for the loads, the merge's launch.
-// 1 x 2048 keys, 2 blocks of 32, 16 / 4 heads: 22.3 -> 18.8 us a call.
+// and straight (8 to 13 KB at D = 128 for 1 to 4 tiles, the general kernel 25 to
+// 32), as each launch fetches it anew.  What bounds it: one round trip for the
+// lengths, one for the loads, the merge's launch.  1 x 2048 keys, 2 blocks of
+// 32, 16 / 4 heads, before the merge took more lanes: 22.3 -> 18.8 us a call.
+// One form per tile count: 192-key units with the loads of four tiles were 1 to
+// 3% slower (2 x 2800 keys, 64 / 8 heads 18.1 / 17.6 us).
 template <int D, int MODE, int VT, int NT>
 __device__ __forceinline__ void short_unit(const AttnParams &p) {
   constexpr int KK = D / 16, DB = D / 32, DH = DB / 2;
@@ -1549,13 +1552,16 @@ hipError_t launch_t(const AttnParams &p, hipStream_t stream) {
   const int64_t grid = p.order_kind == kOrderUnits ? p.order_n : p.slots_per_xcd * kXcds;
   const dim3 g(static_cast<unsigned>(grid)), blk(kT);
   if (p.short_tiles) {
-    if (p.v_token_major) {
-      if (p.short_tiles == 2) hipLaunchKernelGGL((window_attention_short_kernel<D, MODE, 1, 2>), g, blk, 0, stream, p);
-      else hipLaunchKernelGGL((window_attention_short_kernel<D, MODE, 1, 4>), g, blk, 0, stream, p);
-    } else {
-      if (p.short_tiles == 2) hipLaunchKernelGGL((window_attention_short_kernel<D, MODE, 0, 2>), g, blk, 0, stream, p);
-      else hipLaunchKernelGGL((window_attention_short_kernel<D, MODE, 0, 4>), g, blk, 0, stream, p);
-    }
+    auto launch_short = [&](auto tiles) {
+      constexpr int NT = decltype(tiles)::value;
+      if (p.v_token_major) hipLaunchKernelGGL((window_attention_short_kernel<D, MODE, 1, NT>), g, blk, 0, stream, p);
+      else hipLaunchKernelGGL((window_attention_short_kernel<D, MODE, 0, NT>), g, blk, 0, stream, p);
+    };
+    static_assert(kShortTiles == 4, "one form per tile count");
+    if (p.short_tiles == 1) launch_short(std::integral_constant<int, 1>{});
+    else if (p.short_tiles == 2) launch_short(std::integral_constant<int, 2>{});
+    else if (p.short_tiles == 3) launch_short(std::integral_constant<int, 3>{});
+    else launch_short(std::integral_constant<int, 4>{});
   } else if (p.v_token_major) {
     if (p.key_split == 2) hipLaunchKernelGGL((window_attention_kernel<D, MODE, 2, 1, 0>), g, blk, 0, stream, p);
     else hipLaunchKernelGGL((window_attention_kernel<D, MODE, 1, 1, 0>), g, blk, 0, stream, p);

@@ -42,7 +42,7 @@ struct AttnParams {
   int32_t qtiles, splits, kv_chunk;
   int32_t key_split;          // 1 (256-row tiles), or 2 (128-row tiles: few rows per KV head, or little work)
   int32_t v_token_major;      // V pages [16][D] (like K) instead of [D][16]
-  int32_t short_tiles;        // 0, or 2 / 4: the kernel for units of at most that many key tiles (128-row tiles)
+  int32_t short_tiles;        // 0, or 1 to 4: the kernel for units of at most that many key tiles (128-row tiles)
   int32_t pipelined;          // software-pipelined key loop (token-minor V, no key split)
   int64_t groups;             // (split, sequence rank, KV head) groups of qtiles work units
   int64_t slots_per_xcd;      // grid = kXcds * slots_per_xcd workgroups

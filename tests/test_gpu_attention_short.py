@@ -1,5 +1,5 @@
 """The attention kernel for units of at most four key tiles: key counts on both
-sides of its tiles and of its 2- and 4-tile forms, row counts on both sides of
+sides of its tiles and in its 1- to 4-tile forms, row counts on both sides of
 a wave's and a workgroup's rows, one split and many, ragged lengths (dispatch
 table), bounds only, NaN tails, block flags and the gate; against the oracle,
 and against the general kernel over random shapes of the range."""
@@ -45,6 +45,22 @@ def test_row_counts(gpu, group, W, block, vt):
     assert "short" in _plan(gpu, case)["kernel"]
     for mode in ("bidir", "block_causal"):
         assert_attn_close(A.run_case(gpu, case, mode), A.oracle_case(case, mode), f"rows {group * W} vt {vt} {mode}")
+
+
+@pytest.mark.parametrize("split", [64, 128, 192, 256])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("vt", [False, True])
+def test_unit_lengths(gpu, split, D, vt):
+    """One form per tile count of a unit, with a last unit of one key, of one tile
+    less, and whole."""
+    spec = synth.AttnSpec(4, 16, 1, ("fixed", 0), 8, 2, D)
+    case = synth.make_attention_case(spec, split, prefix_lens=[2 * split + 1 - 16, 3 * split - 64, 3 * split - 16, 5],
+                                     window_lens=[16] * 4, tail_fill=float("nan"), v_token_major=vt)
+    kernel = _plan(gpu, case, kv_split_tokens=split)["kernel"]
+    assert "short" in kernel and kernel.endswith(f",{split // 64}>"), kernel
+    for mode in ("bidir", "block_causal"):
+        assert_attn_close(A.run_case(gpu, case, mode, kv_split_tokens=split), A.oracle_case(case, mode),
+                          f"units of {split} D {D} vt {vt} {mode}")
 
 
 @pytest.mark.parametrize("seed", range(16))
