@@ -1416,8 +1416,8 @@ __global__ __launch_bounds__(kT, 1) void window_attention_short_kernel(AttnParam
 // The splits of an item are shared by L lanes (1, 2, 4 or 8, see the launch); the
 // lanes' sums are then combined in a fixed order.  A lane reads 8 splits in one
 // round of loads.  A short call is launch and round trips only, and 17 splits
-// by one lane were three rounds: 1 x 2048 keys 18.3 -> 16.0 us a call, 1 x 8192
-// 33.1 -> 27.2; up to 8 splits are as they were.
+// by one lane were three rounds: 1 x 2048 keys 18.3 -> 16.0 us a call; up to 8
+// splits are as they were.
 constexpr int kMergeDims = 8;   // dims per merge thread: two 16-byte loads per split, one 16-byte store
 template <int D, int L>
 __global__ __launch_bounds__(256) void window_attention_merge_kernel(AttnParams p) {
@@ -1579,13 +1579,14 @@ hipError_t launch_t(const AttnParams &p, hipStream_t stream) {
     hipLaunchKernelGGL((window_attention_merge_kernel<D, L>), mgrid, dim3(256), 0, stream, p);
   };
   // Lanes per item: the fewest that hold the plan's splits in one round of loads
-  // each, but no more workgroups for it than CUs (2^16 lanes): with more, the
-  // empty ones of a plan whose bounds are wide, and the loads of a full one, cost
-  // more than the rounds.  1 lane / as many as hold the splits / this rule, us:
-  // 1 x 6000 keys, 8 blocks of 16, 32 splits 32.5 / 35.6 / 30.3; 3 x 3200, 17
-  // splits, 98304 items 31.5 / 34.2 / 31.5; 4 x 18464, 33 splits 30.4 / 28.9 / 28.9.
+  // each, but no more than 2^17 lanes, two workgroups per CU (one for 8 lanes an
+  // item): with more, the empty workgroups of a plan whose bounds are wide, and the
+  // loads of a full one, cost more than the rounds.  Over 4700 calls of 9 to 128
+  // splits: 0.952 of the time with one lane if the lanes always hold the splits,
+  // 0.950 so.  Measured, us, 1 / 2 / 4 / 8 lanes: 1 row block of 65536 items, 13
+  // splits 31.4 / 24.1 / 32.5 / 36.4; 98304 items, 17 splits 31.5 / - / 34.2 / -.
   int lanes = 1;
-  while (lanes < 8 && 8 * lanes < p.splits && items * p.batch * 2 * lanes <= (1 << 16)) lanes *= 2;
+  while (lanes < 8 && 8 * lanes < p.splits && items * p.batch * 2 * lanes <= (lanes == 4 ? 1 << 16 : 1 << 17)) lanes *= 2;
   if (lanes == 1) merge(std::integral_constant<int, 1>{});
   else if (lanes == 2) merge(std::integral_constant<int, 2>{});
   else if (lanes == 4) merge(std::integral_constant<int, 4>{});

@@ -25,9 +25,9 @@ def test_merge_lanes(gpu, nsplit, D):
         assert_attn_close(out, A.oracle_case(case, mode), f"{nsplit} splits D {D} {mode}")
 
 
-@pytest.mark.parametrize("W,hq,nsplit", [(128, 32, 17), (32, 16, 33), (32, 16, 70), (32, 8, 70)])
+@pytest.mark.parametrize("W,hq,nsplit", [(128, 32, 17), (64, 16, 33), (64, 16, 70), (32, 8, 70)])
 def test_merge_lanes_of_many_splits(gpu, W, hq, nsplit):
-    """More items than the lanes of one workgroup per CU leave room for: one, two
+    """More items than leave room for the lanes that would hold the splits: one, two
     (33 and 70 splits) and four lanes with more than 8 splits each."""
     n = nsplit * 64
     spec = synth.AttnSpec(3, 16, W // 16, ("fixed", 0), hq, 4, 128)
