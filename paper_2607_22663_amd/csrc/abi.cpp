@@ -271,6 +271,17 @@ mbe_status plan_attention(const mbe_paged_kv *kv, const mbe_attn_opts *o, int32_
   bool ragged = false;
   for (size_t b = 1; b < n_seq.size(); ++b) ragged = ragged || n_seq[b] != n_seq[0];
 
+  // Ragged lengths: a dispatch table for splits of c keys (none: finish < 0).
+  UnitSchedule sched;
+  auto schedule = [&](int64_t c, int32_t qtiles, UnitSchedule *out) {
+    std::vector<SeqWork> seqs(o->batch);
+    for (int b = 0; b < o->batch; ++b) {
+      const int64_t W = fixed_window >= 0 ? fixed_window : o->host_window_lens[b];
+      seqs[b] = {n_seq[b], W, static_cast<int32_t>(tiles_of(pl->group * W))};
+    }
+    schedule_units(seqs, kv->num_kv_heads, qtiles, o->num_q_heads, kv->head_dim, max_kv, c, out);
+  };
+
   int64_t chunk = o->kv_split_tokens;
   bool rule_split = false;      // the default rule below cut the key ranges to fill the CUs
   bool alternates = true;       // shorter splits than the rule's may be tried
@@ -289,31 +300,47 @@ mbe_status plan_attention(const mbe_paged_kv *kv, const mbe_attn_opts *o, int32_
       }
       return u;
     };
-    // Workgroups of that plan: every split and query tile within the bounds,
-    // unless a dispatch table (ragged lengths, see below) names the units.
-    auto workgroups = [&](int64_t c) {
-      const int64_t all = static_cast<int64_t>(o->batch) * kv->num_kv_heads * std::max<int64_t>(1, tiles_of(rows)) *
-                          ((max_kv + c - 1) / c);
-      return ragged && all < mbe::kNoUnit ? units(c) : all;
-    };
     const int64_t c_max = std::max<int64_t>(kMinChunk, (max_kv + mbe::kKeyTile - 1) / mbe::kKeyTile * mbe::kKeyTile);
     // Little work: 128-row tiles in units of at most 4 key tiles that all run
-    // at once, on the kernel for such units; the shortest that fit.  Not where the
-    // bounds are so much wider than the lengths that smaller tiles only make
-    // more empty workgroups: 1 x 200 keys, 1 of 8 blocks, bounds of 32768 keys
-    // 22.3 us with 4128 workgroups, 32.6 with 8256; of 4096 keys 14.5 / 14.5 with
-    // 544 / 1088; 2 x 100, 2 of 8 blocks, 4096 keys 18.3 / 22.5 with 2176 / 4352.
+    // at once, on the kernel for such units; the shortest that fit.  Smaller
+    // tiles than the wide rule's are not taken
+    //  - where an XCD would get more units than it has CUs (the query tiles of a
+    //    group stay on one): 3 x 300-500 keys, 6 to 8 blocks of 32, 272 slots 28.9
+    //    us with 256-row tiles, 32.9 with these;
+    //  - where the bounds are so much wider than the lengths that they only make
+    //    more empty workgroups: 1 x 200 keys, 1 of 8 blocks, bounds of 32768 keys
+    //    22.3 us with 4128 workgroups, 32.6 with 8256; of 4096 keys 14.5 / 14.5
+    //    with 544 / 1088; 2 x 100, 2 of 8 blocks 18.3 / 22.5 with 2176 / 4352.
     const int32_t wide_tile = pl->row_tile;
+    auto all_at_once = [&](int64_t c) {
+      if (units(c) > kConcurrentUnits) return false;
+      if (wide_tile == pl->row_tile) return true;
+      const int64_t seq_heads = static_cast<int64_t>(o->batch) * kv->num_kv_heads;
+      const int64_t bound_tiles = std::max<int64_t>(1, tiles_of(rows));
+      if (ragged) {
+        schedule(c, static_cast<int32_t>(bound_tiles), &sched);
+        if (sched.finish >= 0) return sched.order_n <= kConcurrentUnits;
+      }
+      if (seq_heads * ((max_kv + c - 1) / c) * bound_tiles > 5 * kConcurrentUnits) return false;
+      // no table: groups go round the XCDs, those with work first
+      int64_t n = max_kv, tiles = bound_tiles;
+      if (host) {
+        n = *std::max_element(n_seq.begin(), n_seq.end());
+        if (fixed_window < 0)
+          tiles = tiles_of(static_cast<int64_t>(pl->group) *
+                           *std::max_element(o->host_window_lens, o->host_window_lens + o->batch));
+      }
+      return (seq_heads * ((n + c - 1) / c) + mbe::kXcds - 1) / mbe::kXcds * tiles <= kCusPerXcd;
+    };
     if (pipeline_override() < 0) {
       pl->row_tile = mbe::kShortRows;
       for (int64_t c = kMinChunk; c <= mbe::kShortTiles * mbe::kKeyTile && chunk == 0; c += mbe::kKeyTile)
-        if (units(c) <= kConcurrentUnits && (wide_tile == mbe::kShortRows || workgroups(c) <= 5 * kConcurrentUnits))
-          chunk = c;
+        if (all_at_once(c)) chunk = c;
     }
     if (chunk != 0) {
       rule_split = true;
       alternates = false;
-    } else if (pl->row_tile = wide_tile; units(c_max) > kConcurrentUnits) {
+    } else if (pl->row_tile = wide_tile, sched.finish = -1.0; units(c_max) > kConcurrentUnits) {
       // More units than CUs already: no split (each split adds a pipeline fill
       // and a merge of partial results, and the longest-first order balances
       // the units of a large batch).
@@ -341,20 +368,14 @@ mbe_status plan_attention(const mbe_paged_kv *kv, const mbe_attn_opts *o, int32_
   // finishes first (the default unless another beats it by kMinPlanGain).
   // Equal lengths are balanced by the formula already, and large batches
   // gained nothing from a table.
-  UnitSchedule sched;
   if (ragged && rule_split) {
-    std::vector<SeqWork> seqs(o->batch);
-    for (int b = 0; b < o->batch; ++b) {
-      const int64_t W = fixed_window >= 0 ? fixed_window : o->host_window_lens[b];
-      seqs[b] = {n_seq[b], W, static_cast<int32_t>(tiles_of(pl->group * W))};
-    }
-    schedule_units(seqs, kv->num_kv_heads, pl->qtiles, o->num_q_heads, kv->head_dim, max_kv, chunk, &sched);
+    if (sched.finish < 0) schedule(chunk, pl->qtiles, &sched);
     UnitSchedule alt;
     const int64_t d = chunk;
     for (int64_t cand : {d * 7 / 8, d * 3 / 4}) {
       const int64_t c = std::max<int64_t>(kMinChunk, (cand + mbe::kKeyTile - 1) / mbe::kKeyTile * mbe::kKeyTile);
       if (c >= d || !alternates) continue;
-      schedule_units(seqs, kv->num_kv_heads, pl->qtiles, o->num_q_heads, kv->head_dim, max_kv, c, &alt);
+      schedule(c, pl->qtiles, &alt);
       if (alt.finish >= 0 && (sched.finish < 0 || alt.finish < sched.finish * (1.0 - kMinPlanGain))) {
         chunk = c;
         sched = alt;

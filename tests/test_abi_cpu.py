@@ -458,3 +458,26 @@ def test_wide_bounds_do_not_halve_the_tiles(lib, monkeypatch):
     assert plan([100, 100], [64, 64], 4096, 256, group=8) == (1, 2176)
     assert plan([100, 150], [64, 64], 4096, 256, group=8) == (2, 64)
     assert plan([100, 150], [64, 64], 131072, 256, group=8) == (1, 65664)     # unit indices beyond the table's 16 bits
+
+
+@pytest.mark.parametrize("ragged", [True, False])
+def test_small_tiles_fit_every_xcd(lib, monkeypatch, ragged):
+    """128-row tiles where 256-row ones are possible: no XCD gets more than its
+    32 CUs' units (8 slots of the grid are one per XCD), with a dispatch table of
+    ragged lengths and without."""
+    monkeypatch.delenv("MBE_ATTN_PIPELINE", raising=False)
+    rng = np.random.default_rng(17)
+    small = 0
+    for _ in range(400):
+        batch, hkv, group = int(rng.integers(1, 9)), int(rng.choice([1, 2, 4, 8])), int(rng.choice([4, 8]))
+        W = [32 * int(rng.integers(2, 9)) for _ in range(batch)] if ragged else [32 * int(rng.integers(2, 9))] * batch
+        P = [int(rng.integers(0, 1200)) for _ in range(batch)] if ragged else [int(rng.integers(0, 1200))] * batch
+        kp = torch.empty((8, hkv, 16, 128), dtype=torch.bfloat16, device="meta")
+        vp = torch.empty((8, hkv, 128, 16), dtype=torch.bfloat16, device="meta")
+        pt = torch.empty((batch, -(-(max(P) + max(W)) // 16)), dtype=torch.int32, device="meta")
+        p = mbe.window_attention_plan(group * hkv, kp, vp, pt, batch, sum(W), max_prefix_len=max(P),
+                                      max_window_len=max(W), host_prefix_lens=P, host_window_lens=W)
+        if p["key_split"] == 2 and group * max(W) > 128:
+            small += 1
+            assert p["workgroups"] <= 256, (P, W, hkv, group, p)
+    assert small > 50
