@@ -31,7 +31,8 @@
  *     that share a workspace must not overlap in time.
  *   - The attention and edit-selection calls launch one kernel, plus a small
  *     merge/finalize kernel when the work is split across workgroups (see the
- *     workspace sizes).  mbe_threshold_update adds one per-block kernel.
+ *     workspace sizes).  mbe_threshold_update launches one kernel for its rows and
+ *     one per-block kernel, which merges rows that were split.
  */
 #ifndef MBE_H_
 #define MBE_H_
@@ -264,8 +265,11 @@ mbe_status mbe_threshold_update(const void *logits, int64_t rows, int64_t vocab,
                                 float *entropy, const int32_t *run_if_nonzero, void *workspace,
                                 size_t workspace_bytes, void *stream);
 
-/* Workspace bytes mbe_threshold_update needs (the per-row predictions plus
- * the per-chunk partials of mbe_edit_select).  (size_t)-1 for negative sizes. */
+/* Workspace bytes mbe_threshold_update needs: the per-row predictions plus the
+ * partials of the chunks the update cuts few rows into.  It cuts more rows than
+ * mbe_edit_select does (its per-block step merges the chunks without a launch of
+ * their own), so its partials can be larger than
+ * mbe_edit_select_workspace_size.  (size_t)-1 for negative sizes. */
 size_t mbe_threshold_update_workspace_size(int64_t rows, int64_t vocab);
 
 /* mbe_threshold_update for callers that cannot allocate device memory and

@@ -55,9 +55,8 @@ __global__ __launch_bounds__(256) void tail_entropy_kernel(const float *entropy,
 
 // Blocks of at most 64 rows: one wave per block, the same network across its
 // lanes, no barriers.  The kernel is latency only (a few KB): a launch, one
-// load, the network.  with the update's step done
-// the same way, 992 rows of 100003 with scores 48.5 -> 45.0 us, 2048 x 131072
-// 96.3 -> 92.4 us.
+// load, the network.  Together with the update's step done the same way, 992
+// rows of 100003 with scores 48.5 -> 45.0 us, 2048 x 131072 96.3 -> 92.4 us.
 __global__ __launch_bounds__(256) void tail_entropy_wave_kernel(const float *entropy, int64_t num_blocks,
                                                                 int32_t block_size, int32_t k, float *scores) {
   const int lane = threadIdx.x & 63;
