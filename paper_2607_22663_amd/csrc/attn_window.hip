@@ -1234,7 +1234,8 @@ __device__ __forceinline__ void short_unit(const AttnParams &p) {
   }
   const int r = row0 + wrow * 32 + c;          // this lane's row
   const bool valid = row_valid(r);
-  const int64_t rowidx = static_cast<int64_t>(cu + (valid ? r / G : 0)) * p.num_q_heads + g * G + (valid ? r % G : 0);
+  // (an invalid lane reads row 0: its column of the scores is its own and goes nowhere)
+  const int64_t rowidx = valid ? static_cast<int64_t>(cu + r / G) * p.num_q_heads + g * G + r % G : 0;
 
   // ---- key range [kb, ke), its tiles that any row of the workgroup sees, and
   // the keys [kb, seen) that every row sees
@@ -1269,8 +1270,8 @@ __device__ __forceinline__ void short_unit(const AttnParams &p) {
                                        16, 0, kStreamLoad);
   bf16x8 qreg[KK];
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk)
-    qreg[kk] = valid ? *reinterpret_cast<const bf16x8 *>(p.q + rowidx * D + kk * 16 + h * 8) : bf16x8{};
+  for (int kk = 0; kk < KK; ++kk)          // (no branch: some forms waited for all of K in it)
+    qreg[kk] = *reinterpret_cast<const bf16x8 *>(p.q + rowidx * D + kk * 16 + h * 8);
   asm volatile("" ::: "memory");           // V is requested after all of K
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

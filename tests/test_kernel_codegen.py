@@ -21,6 +21,11 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
+@pytest.fixture(scope="module")
+def asm(tmp_path_factory):
+    return _asm(tmp_path_factory.mktemp("asm"))
+
+
 def _asm(tmp_path):
     from paper_2607_22663_amd import build as b
     try:
@@ -36,8 +41,8 @@ def _asm(tmp_path):
     return out.read_text()
 
 
-def _kernels(asm):
-    for m in re.finditer(r"^(_ZN3mbe12_GLOBAL__N_123window_attention_kernel\w+):", asm, re.M):
+def _kernels(asm, name="23window_attention_kernel"):
+    for m in re.finditer(r"^(_ZN3mbe12_GLOBAL__N_1%s\w+):" % name, asm, re.M):
         start = m.start()
         yield m.group(1), asm[start:asm.index(".Lfunc_end", start)]
 
@@ -56,8 +61,7 @@ def _blocks(body):
 
 @pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"),
                     reason="needs hipcc")
-def test_attention_main_loops_never_drain_the_loads(tmp_path):
-    asm = _asm(tmp_path)
+def test_attention_main_loops_never_drain_the_loads(asm):
     kernels = list(_kernels(asm))
     # D x mask mode x key split x V layout, plus the pipelined loop (token-minor
     # V, no key split) for each D and mask mode
@@ -83,3 +87,24 @@ def test_attention_main_loops_never_drain_the_loads(tmp_path):
         # code spill a few values (7 and 11 dwords as built)
         limit = 64
         assert _scratch_bytes(asm, name) <= limit, f"{name} spills more than {limit // 4} dwords per lane"
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"),
+                    reason="needs hipcc")
+def test_short_unit_kernels_request_everything_first(asm):
+    kernels = list(_kernels(asm, "29window_attention_short_kernel"))
+    # D x mask mode x V layout x 1 to 4 tiles
+    assert len(kernels) == 32, [k for k, _ in kernels]
+    for name, body in kernels:
+        d, tiles = int(re.search(r"ILi(\d+)E", name).group(1)), int(re.search(r"ELi(\d)EEEv", name).group(1))
+        per_tile = d // 64                          # 1 KB loads of a wave per tile and operand
+        ins = [l.strip() for l in body.splitlines() if l.strip() and not l.strip().startswith((";", "."))]
+        loads = [i for i, l in enumerate(ins) if l.startswith("global_load_lds")]
+        assert len(loads) == 2 * tiles * per_tile, (name, len(loads))
+        between = ins[loads[0]:loads[-1]]
+        waits = [l for l in between if l.startswith("s_waitcnt") and "vmcnt" in l]
+        assert not waits, f"{name}: waits between its loads: {waits}"
+        assert not any(l.startswith("v_mfma") for l in between), name
+        first = next(l for l in ins[loads[-1]:] if l.startswith("s_waitcnt") and "vmcnt" in l)
+        assert f"vmcnt({tiles * per_tile})" in first, f"{name}: {first} before the scores"
+        assert _scratch_bytes(asm, name) == 0, f"{name} spills"
