@@ -19,25 +19,37 @@ def _attn_args(dev):
 
 
 def test_host_tensors_are_refused():
+    """On a machine with a GPU and without: the binding itself refuses them, by
+    the stream it cannot get for them, before the library is called."""
     a = _attn_args("cpu")
     kw = dict(max_prefix_len=64)
-    with pytest.raises(Exception):
-        mbe.window_attention(*a, 32, max_window_len=32, **kw)
-    with pytest.raises(Exception):
-        mbe.block_diffusion_attention(*a[:5], 32, **kw)
     logits, cur = torch.zeros(32, 64, dtype=torch.bfloat16), torch.zeros(32, dtype=torch.int32)
-    with pytest.raises(Exception):
-        mbe.edit_select(logits, cur, 0.5)
-    with pytest.raises(Exception):
-        mbe.threshold_update(logits, cur, 63, 32, 0.5, 0.0)
-    with pytest.raises(Exception):
-        mbe.tail_entropy_scores(torch.zeros(32), 32, 0.5)
-    with pytest.raises(Exception):
-        mbe.select_start_block(torch.zeros(1, 4), torch.zeros(1, dtype=torch.int32), 2)
-    with pytest.raises(Exception):
-        mbe.refresh_blocks(torch.zeros(1, 4, dtype=torch.uint8))
-    with pytest.raises(Exception):
-        mbe.kv_write(a[1], a[2], a[3], a[4], a[5], a[0][:, :2].contiguous(), a[0][:, :2].contiguous(), max_len=32)
+    calls = [lambda: mbe.window_attention(*a, 32, max_window_len=32, **kw),
+             lambda: mbe.block_diffusion_attention(*a[:5], 32, **kw),
+             lambda: mbe.edit_select(logits, cur, 0.5),
+             lambda: mbe.threshold_update(logits, cur, 63, 32, 0.5, 0.0),
+             lambda: mbe.tail_entropy_scores(torch.zeros(32), 32, 0.5),
+             lambda: mbe.select_start_block(torch.zeros(1, 4), torch.zeros(1, dtype=torch.int32), 2),
+             lambda: mbe.refresh_blocks(torch.zeros(1, 4, dtype=torch.uint8)),
+             lambda: mbe.kv_write(a[1], a[2], a[3], a[4], a[5], a[0][:, :2].contiguous(), a[0][:, :2].contiguous(),
+                                  max_len=32)]
+    reached = []
+
+    class Lib:
+        """The library, with calls that would launch recorded instead."""
+        def __getattr__(self, name):
+            f = getattr(real, name)
+            return f if "workspace" in name or name == "mbe_last_error" else lambda *x: reached.append(name) or 0
+
+    real, mbe._lib = mbe.load(), Lib()
+    try:
+        for call in calls:
+            with pytest.raises((ValueError, RuntimeError, AssertionError)) as e:
+                call()
+            assert not isinstance(e.value, mbe.MbeError), e.value
+    finally:
+        mbe._lib = real
+    assert not reached, reached
 
 
 NAMES = ["q", "k_pages", "v_pages", "page_table", "prefix_lens", "window_lens", "out"]
