@@ -1173,6 +1173,8 @@ __device__ __forceinline__ void read_fields(const AttnParams &p) {
 // 3% slower (2 x 2800 keys, 64 / 8 heads 18.1 / 17.6 us).
 template <int D, int MODE, int VT, int NT>
 __device__ __forceinline__ void short_unit(const AttnParams &p) {
+  MBE_TL_REAL(0);
+  MBE_TL_CYCLES(6);
   constexpr int KK = D / 16, DB = D / 32, DH = DB / 2;
   constexpr int PB = Tile<D>::kPageBytes, WL = Tile<D>::kWaveLoads;
   constexpr int kSlices = kWaves / 2;                          // 32-row slices of the tile
@@ -1212,6 +1214,7 @@ __device__ __forceinline__ void short_unit(const AttnParams &p) {
   const int n_all = P + W;
   const int nsplit = min(p.splits, max(1, (n_all + p.kv_chunk - 1) / p.kv_chunk));
   if (row0 >= M || split >= nsplit) return;
+  MBE_TL_REAL(1);
 
   int cu = 0;      // first query row of sequence b
   if (fixed) {
@@ -1284,6 +1287,7 @@ __device__ __forceinline__ void short_unit(const AttnParams &p) {
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(wait_vmcnt(NT * WL));     // K is in LDS
   lds_barrier();
+  MBE_TL_REAL(2);
 
   // ---- scores of this wave's 32-key block of every tile
   const int krow = perm_row(c);
@@ -1355,6 +1359,7 @@ __device__ __forceinline__ void short_unit(const AttnParams &p) {
     }
   }
   l += __shfl_xor(l, 32);
+  MBE_TL_REAL(3);
 
   // ---- the two waves of a row slice exchange halves of O (wave w keeps the
   // first half of the dims, wave w + 4 the second) and their sums, each
@@ -1393,6 +1398,7 @@ __device__ __forceinline__ void short_unit(const AttnParams &p) {
     half_out(lt > 0.f ? 1.f / lt : 0.f, [&](int d0, const float (&o)[4]) {
       *reinterpret_cast<uint2 *>(orow + d0) = make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
     });
+    MBE_TL_END();
     return;
   }
   const int64_t part = split * (static_cast<int64_t>(p.total_q) * p.num_q_heads) + rowidx;
@@ -1400,6 +1406,7 @@ __device__ __forceinline__ void short_unit(const AttnParams &p) {
     *reinterpret_cast<float4 *>(p.part_o + part * D + d0) = make_float4(o[0], o[1], o[2], o[3]);
   });
   if (h == 0 && kown == 0) *reinterpret_cast<float2 *>(p.part_ml + part * 2) = make_float2(mt, lt);
+  MBE_TL_END();
 }
 
 template <int D, int MODE, int VT, int NT>
