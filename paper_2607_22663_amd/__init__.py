@@ -296,6 +296,7 @@ def window_attention_plan(num_q_heads, k_pages, v_pages, page_table, batch, tota
     _check("mbe_window_attention_plan", lib.mbe_window_attention_plan(ctypes.byref(kv), ctypes.byref(opts),
                                                                       ctypes.byref(plan)))
     d = {f: getattr(plan, f) for f, _ in AttnPlan._fields_}
+    # (the library's rule for the short kernel; tests/host_fuzz checks that they agree)
     if plan.key_split == 2 and plan.kv_chunk <= 256 and os.environ.get("MBE_ATTN_PIPELINE", "")[:1] not in ("0", "1"):
         d["kernel"] = (f"window_attention_short_kernel<{k_pages.shape[3]},{mode},{int(layout == V_TOKEN_MAJOR)},"
                        f"{plan.kv_chunk // 64}>")
